@@ -28,13 +28,18 @@
 // than it saves (every slice re-reads the indices and repeats the shuffles), so
 // rows are read whole.
 //
-// Gathers.  A group takes the entries of its row (or task) in rounds of kRound:
-// each lane loads kRound / LPR (column, value) pairs with coalesced loads, the
-// pairs are broadcast inside the group with shuffles, and all kRound neighbour
-// slices are requested before the first product, so every group keeps kRound
-// loads in flight (the ILP of the paper's dense path, Alg. 1, deepened).  On large
-// operands the rows of cold columns (marked by the plan) are read non-temporally
-// (the cache classes below).
+// Gathers.  A group takes the entries of its row (or task) in rounds of R = 16 (12 on
+// large operands): each lane loads R / LPR (column, value) pairs with coalesced loads, the
+// pairs are broadcast inside the group with shuffles, and all R neighbour
+// slices are requested before the first product, so every group keeps R
+// loads in flight (the ILP of the paper's dense path, Alg. 1, deepened).  Nothing in a round
+// branches (see gather), and the next round's pairs are requested with this round's slices.
+// On large operands the rows of cold columns (marked by the plan) are read non-temporally
+// (the cache classes below).  Before the rounds were free of branches a lone wavefront took
+// 1.65 us a round (F = 128) and the launches on small and middling graphs were bound by that
+// chain.  Measured before and after: R-MAT n = 30,007 (longest row 3,928), F = 128: 227 ->
+// 112 us; R-MAT n = 4,096, F = 16: 15.8 -> 12.5 us; block model n = 2^18 (18.8M entries),
+// F = 128: 496 -> 448 us (21.5 TB/s of gathers, out of the L2s).
 //
 // Dense path (paper: one row per block, 4-way ILP and a shared reduction): a long
 // row gets a wavefront whose groups take rounds of the row in turn and are summed
@@ -48,22 +53,29 @@
 // Y is bit-reproducible.
 //
 // Sparse path (tasks): the group walks the task's entries as one stream, so even
-// rows with one or two entries share a round of kRound gathers; a row is written
+// rows with one or two entries share a round of R gathers; a row is written
 // as soon as its last entry has been added.
 //
-// Summation: products and the sum of one round (<= kRound terms) are float32,
+// Summation: products and the sum of one round (<= 16 terms) are float32,
 // rounds are added in float64, and each output is rounded once to float32.  The
-// error of every element is below ~(kRound + 2) * 2^-24 * sum |a||x|.
+// error of every element is below ~(16 + 2) * 2^-24 * sum |a||x|.
 #include "internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace dgc {
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr int kRound = 16;            // entries a lane group gathers per round
+// Entries a lane group gathers per round.  Operands larger than the memory-side cache take 12:
+// what 16 wavefronts per CU then have in flight (6 MiB per XCD) pushes less out of the 4 MiB L2.
+// Measured on R-MAT n = 2^21 and 2^22, F = 64, branch-free gathers: 16 per round 1.70 and 2.06
+// ms, 12 per round 1.69 and 2.03, 8 per round 1.71 and 2.05; smaller operands are faster
+// with 16 (block model n = 2^18, F = 128: 0.450 against 0.460 ms).
+constexpr int kRound = 16;
+constexpr int kRoundLarge = 12;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -203,102 +215,149 @@ struct StageRows {
 constexpr int kCpolNt = 2;                    // the nt field of a gfx950 buffer load
 constexpr uint32_t kRowMask = 0x7FFFFFFFu;
 
-// Entries [e, min(e + kRound, e_end)) of the sorted copy, as seen by lane li of a
-// group whose first lane is gbase: lane li loads entries e + li + k LPR; entry u is
-// then held by lane u % LPR in register u / LPR.  An invalid entry holds column -1.
-template <int LPR>
+// How a launch's gathers address X.  kBuffer: buffer loads at 32-bit byte offsets (X up to
+// kMaxBufferBytes); kClasses: the same with the cache classes above; kWide: 64-bit addresses.
+enum GatherMode { kBuffer = 0, kClasses = 1, kWide = 2 };
+constexpr int round_entries(int mode) {
+    return mode == kBuffer ? kRound : kRoundLarge;
+}
+
+// Offset of an entry that reads nothing: past the end of every buffer, also with a lane's
+// offset inside a window (below 1 KiB) added, so that a buffer load of it returns zeros.
+constexpr uint32_t kNoEntry = 0xFFFFF000u;
+constexpr uint64_t kMaxBufferBytes = kNoEntry;
+constexpr uint32_t kNoRow = 0x80000000u;        // marks an invalid entry's row in kWide
+
+// Entries [e, min(e + R, e_end)) of the sorted copy (e_end > 0), as seen by lane li of a
+// group: lane li loads entries e + li + k LPR; entry u is then held by lane u % LPR in
+// register u / LPR.  The loads are unconditional (past the end they read the last entry).
+template <int LPR, int R>
 struct Round {
-    static constexpr int EPL = (kRound + LPR - 1) / LPR;   // entries per lane
+    static constexpr int EPL = (R + LPR - 1) / LPR;   // entries per lane
     int32_t c[EPL];
     float v[EPL];
 
     __device__ __forceinline__ void load(const Args &a, int32_t e, int32_t e_end, int li) {
 #pragma unroll
         for (int k = 0; k < EPL; ++k) {
-            const int slot = li + k * LPR;
-            const int32_t idx = e + slot;
-            const bool ok = slot < kRound && idx < e_end;
-            c[k] = ok ? a.pcol[idx] : -1;
-            v[k] = ok ? a.pval[idx] : 0.f;
+            const int32_t idx = min(e + li + k * LPR, e_end - 1);
+            c[k] = a.pcol[idx];
+            v[k] = a.pval[idx];
         }
     }
 };
 
-template <int POLICY>
-__device__ __forceinline__ void load_x_cp(__amdgpu_buffer_rsrc_t rx, uint32_t off, float (&x)[4]) {
-    const f32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, POLICY);
-    x[0] = v[0];
-    x[1] = v[1];
-    x[2] = v[2];
-    x[3] = v[3];
+template <int VEC, int POLICY>
+__device__ __forceinline__ void load_x_buf(__amdgpu_buffer_rsrc_t rx, uint32_t off, float (&x)[VEC]) {
+    if constexpr (VEC == 4) {
+        const f32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, POLICY);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = v[j];
+    } else {
+        static_assert(VEC == 1, "one or four features per lane");
+        x[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, off, 0, POLICY));
+    }
 }
 
-// Requests the kRound neighbour slices of a round (invalid entries read nothing and
-// get weight zero).
+// Requests the R neighbour slices of a round (invalid entries read nothing and get
+// weight zero).
 // The broadcasts read lane gbase + u % LPR with ds_bpermute: the group's base byte
 // address is hidden from the optimiser, so that the constant u % LPR lanes go into the
 // instruction's offset field instead of one precomputed address register per u
 // (sixteen registers held through the whole kernel otherwise).
-template <int LPR, int VEC, bool CP>
-__device__ __forceinline__ void gather(const Args &a, const Round<LPR> &r, int gbase, int f,
-                                       bool fin, float (&as)[kRound], float (&xs)[kRound][VEC]) {
-    static_assert(!CP || VEC == 4, "cache classes need 16-byte loads");
+// The buffer modes broadcast byte offsets (one multiply per entry instead of one per lane and
+// entry), and an entry past the end is an offset past the buffer instead of a branch: with a
+// branch per gather the compiler waited for the first gather inside its branch and for
+// every broadcast before the next one, so a round took two memory latencies and sixteen
+// LDS latencies (1.65 us on an idle chip, F = 128).
+template <int LPR, int VEC, int MODE, int R>
+__device__ __forceinline__ void gather(const Args &a, const Round<LPR, R> &r, int32_t e, int32_t e_end, int li,
+                                       int gbase, int f, bool fin, float (&as)[R],
+                                       float (&xs)[R][VEC]) {
+    static_assert(MODE != kClasses || VEC == 4, "cache classes need 16-byte loads");
     int base4 = gbase * 4;
     asm volatile("" : "+v"(base4));
+    constexpr int EPL = Round<LPR, R>::EPL;
+    uint32_t o[EPL];
+    float v[EPL];
 #pragma unroll
-    for (int u = 0; u < kRound; ++u) {
-        const int src = base4 + (u % LPR) * 4;
-        const int32_t cc = __builtin_amdgcn_ds_bpermute(src, r.c[u / LPR]);
-        as[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(r.v[u / LPR])));
-        if constexpr (CP) {
-            if (cc != -1 && fin) {
-                // the host checked that n ld 4 bytes fit the 32-bit range of the buffer
-                const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-                    const_cast<float *>(a.X), 0, static_cast<int>(a.x_bytes), 0x00020000);
-                const uint32_t row = static_cast<uint32_t>(cc) & kRowMask;
-                const uint32_t off = (row * static_cast<uint32_t>(a.ld) + static_cast<uint32_t>(f)) * 4u;
-                if (cc >= 0) load_x_cp<0>(rx, off, xs[u]);
-                else load_x_cp<kCpolNt>(rx, off, xs[u]);      // a marked (cold) column
-            } else {
-                as[u] = 0.f;
-#pragma unroll
-                for (int j = 0; j < VEC; ++j) xs[u][j] = 0.f;
-            }
+    for (int k = 0; k < EPL; ++k) {
+        const bool ok = li + k * LPR < R && e + li + k * LPR < e_end;
+        v[k] = ok ? r.v[k] : 0.f;
+        const uint32_t row = static_cast<uint32_t>(r.c[k]) & kRowMask;
+        if constexpr (MODE == kWide) {
+            o[k] = ok ? row : row | kNoRow;
         } else {
-            if (cc != -1 && fin) {
-                load_x<VEC>(a.X + static_cast<int64_t>(static_cast<uint32_t>(cc) & kRowMask) * a.ld + f, xs[u]);
-            } else {
-                as[u] = 0.f;
+            uint32_t at = row * (static_cast<uint32_t>(a.ld) * 4u);
+            if constexpr (MODE == kClasses) at |= static_cast<uint32_t>(r.c[k]) >> 31;   // a marked (cold) column
+            o[k] = ok ? at : kNoEntry;
+        }
+    }
+    if constexpr (MODE == kWide) {
 #pragma unroll
-                for (int j = 0; j < VEC; ++j) xs[u][j] = 0.f;
+        for (int u = 0; u < R; ++u) {
+            const int src = base4 + (u % LPR) * 4;
+            const uint32_t row = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, static_cast<int>(o[u / LPR])));
+            as[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(v[u / LPR])));
+            // an invalid entry reads the row of the last one and drops it
+            const bool ok = (row & kNoRow) == 0;
+            load_x<VEC>(a.X + static_cast<int64_t>(row & kRowMask) * a.ld + (fin ? f : a.f0), xs[u]);
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) xs[u][j] = ok ? xs[u][j] : 0.f;
+        }
+    } else {
+        // the window's first feature is the buffer's start; a lane without features of its
+        // own reads the window's first ones, which nothing uses
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(a.X) + a.f0, 0, static_cast<int>(a.x_bytes - static_cast<uint32_t>(a.f0) * 4u), 0x00020000);
+        const uint32_t lane_off = fin ? static_cast<uint32_t>(f - a.f0) * 4u : 0u;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int src = base4 + (u % LPR) * 4;
+            const uint32_t at = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, static_cast<int>(o[u / LPR])));
+            as[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(v[u / LPR])));
+            if constexpr (MODE == kBuffer) {
+                load_x_buf<VEC, 0>(rx, at + lane_off, xs[u]);
+            } else {
+                const uint32_t off = (at & ~1u) + lane_off;
+                if (at & 1u) load_x_buf<VEC, kCpolNt>(rx, off, xs[u]);
+                else load_x_buf<VEC, 0>(rx, off, xs[u]);
             }
         }
     }
 }
 
-// Dense path: one wavefront accumulates entries [e0, e1) of one row; on return every
-// lane holds the row's sums for its features (groups reduced by a butterfly).
-template <int LPR, int VEC, bool CP>
-__device__ __forceinline__ void dense_row(const Args &a, int32_t e0, int32_t e1, int li, int gw,
-                                          int gbase, int f, bool fin, double (&tot)[VEC]) {
-    constexpr int GPW = 64 / LPR;
+// Dense path: one lane group accumulates the rounds of 16 entries at e0, e0 + STEP, ...
+// below e1 of one row into tot.  With PF the next round's columns and values are requested
+// behind the current round's gathers, so that a round waits for one memory latency, not two.
+template <int LPR, int VEC, int MODE, bool PF, int R>
+__device__ __forceinline__ void dense_rounds(const Args &a, int32_t e0, int32_t e1, int32_t step, int li,
+                                             int gbase, int f, bool fin, double (&tot)[VEC]) {
 #pragma unroll
     for (int j = 0; j < VEC; ++j) tot[j] = 0.0;
-    for (int32_t e = e0 + gw * kRound; e < e1; e += GPW * kRound) {
-        Round<LPR> r;
-        r.load(a, e, e1, li);
-        float as[kRound], xs[kRound][VEC];
-        gather<LPR, VEC, CP>(a, r, gbase, f, fin, as, xs);
+    if (e0 >= e1) return;
+    Round<LPR, R> r;
+    if constexpr (PF) r.load(a, e0, e1, li);
+    for (int32_t e = e0; e < e1; e += step) {
+        if constexpr (!PF) r.load(a, e, e1, li);
+        float as[R], xs[R][VEC];
+        gather<LPR, VEC, MODE, R>(a, r, e, e1, li, gbase, f, fin, as, xs);
+        if constexpr (PF) r.load(a, e + step, e1, li);
         float acc[VEC];
 #pragma unroll
         for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
 #pragma unroll
-        for (int u = 0; u < kRound; ++u)
+        for (int u = 0; u < R; ++u)
 #pragma unroll
             for (int j = 0; j < VEC; ++j) acc[j] = fmaf(as[u], xs[u][j], acc[j]);
 #pragma unroll
         for (int j = 0; j < VEC; ++j) tot[j] += static_cast<double>(acc[j]);
     }
+}
+
+// The wavefront's groups summed by a butterfly: every lane then holds the sums of its features.
+template <int LPR, int VEC>
+__device__ __forceinline__ void sum_groups(double (&tot)[VEC]) {
 #pragma unroll
     for (int m = LPR; m < 64; m <<= 1)
 #pragma unroll
@@ -317,7 +376,7 @@ __device__ __forceinline__ int32_t task_meta(const int32_t (&m)[N], int j, int g
 
 // The work of logical workgroup lb (feature slice `slice`) for wavefront `wave` of a
 // workgroup of WAVES wavefronts; finished rows go to `emit`.
-template <int LPR, int VEC, int WAVES, bool CP, class Emit>
+template <int LPR, int VEC, int WAVES, int MODE, bool PF, int R, class Emit>
 __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int wave,
                                            const Emit &emit) {
     constexpr int GPW = 64 / LPR;                 // lane groups per wavefront
@@ -336,25 +395,8 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
         const int64_t gi = (static_cast<int64_t>(lb - a.nb_parts - a.nb_long) * WAVES + wave) * GPW + gw;
         const int64_t i = a.n - a.n_long - 1 - gi;
         if (i < a.n_sparse) return;           // the whole group leaves together
-        const int32_t e0 = a.pptr[i], e1 = a.pptr[i + 1];
         double tot[VEC];
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) tot[j] = 0.0;
-        for (int32_t e = e0; e < e1; e += kRound) {
-            Round<LPR> r;
-            r.load(a, e, e1, li);
-            float as[kRound], xs[kRound][VEC];
-            gather<LPR, VEC, CP>(a, r, gbase, f, fin, as, xs);
-            float acc[VEC];
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
-#pragma unroll
-            for (int u = 0; u < kRound; ++u)
-#pragma unroll
-                for (int j = 0; j < VEC; ++j) acc[j] = fmaf(as[u], xs[u][j], acc[j]);
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) tot[j] += static_cast<double>(acc[j]);
-        }
+        dense_rounds<LPR, VEC, MODE, PF, R>(a, a.pptr[i], a.pptr[i + 1], R, li, gbase, f, fin, tot);
         emit.row(a.perm[i], gw * kTaskRows, tot, f, fin);
         return;
     }
@@ -379,7 +421,8 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
             if (e1 - e0 > a.dense_chunk) return;   // covered by its parts
         }
         double tot[VEC];
-        dense_row<LPR, VEC, CP>(a, e0, e1, li, gw, gbase, f, fin, tot);
+        dense_rounds<LPR, VEC, MODE, PF, R>(a, e0 + gw * R, e1, GPW * R, li, gbase, f, fin, tot);
+        sum_groups<LPR, VEC>(tot);
         if (part < 0) {
             if (gw == 0) emit.row(a.perm[i], 0, tot, f, fin);
             return;
@@ -424,13 +467,15 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
         tot[j] = 0.0;
         part[j] = 0.f;
     }
-    for (int32_t e = e_begin; e < e_end; e += kRound) {
-        Round<LPR> r;
-        r.load(a, e, e_end, li);
-        float as[kRound], xs[kRound][VEC];
-        gather<LPR, VEC, CP>(a, r, gbase, f, fin, as, xs);
+    Round<LPR, R> r;
+    if constexpr (PF) r.load(a, e_begin, e_end, li);
+    for (int32_t e = e_begin; e < e_end; e += R) {
+        if constexpr (!PF) r.load(a, e, e_end, li);
+        float as[R], xs[R][VEC];
+        gather<LPR, VEC, MODE, R>(a, r, e, e_end, li, gbase, f, fin, as, xs);
+        if constexpr (PF) r.load(a, e + R, e_end, li);
 #pragma unroll
-        for (int u = 0; u < kRound; ++u) {
+        for (int u = 0; u < R; ++u) {
 #pragma unroll
             for (int j = 0; j < VEC; ++j) part[j] = fmaf(as[u], xs[u][j], part[j]);
             if (e + u + 1 == cur_end) {       // the current row ends with this entry
@@ -456,12 +501,12 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
     }
 }
 
-template <int LPR, int VEC, bool BF, bool CP>
+template <int LPR, int VEC, bool BF, int MODE>
 __global__ __launch_bounds__(kThreads) void spmm_dual_kernel(const Args a) {
     const StoreRows<VEC, BF> emit{a.Y, a.ld, a.relu != 0};
-    spmm_block<LPR, VEC, kWaves, CP>(a, static_cast<int>(blockIdx.x) / a.S,
-                                 static_cast<int>(blockIdx.x) % a.S,
-                                 static_cast<int>(threadIdx.x) >> 6, emit);
+    spmm_block<LPR, VEC, kWaves, MODE, MODE == kBuffer && LPR >= 4, round_entries(MODE)>(
+        a, static_cast<int>(blockIdx.x) / a.S, static_cast<int>(blockIdx.x) % a.S,
+        static_cast<int>(threadIdx.x) >> 6, emit);
 }
 
 // The rows split into parts: row = the sum of its parts' float64 partials, in part order.
@@ -529,7 +574,7 @@ size_t xw_lds_bytes(int lpr, int K, int N) {
            (xw_stage_in_tile(K) ? 0 : static_cast<size_t>(kWaves) * kXwStageWords * sizeof(float));
 }
 
-template <int LPR, bool CP>
+template <int LPR, int MODE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void spmm_xw_kernel(const Args a, const float *__restrict__ W,
                                                            float *__restrict__ T, int32_t K,
@@ -556,7 +601,7 @@ void spmm_xw_kernel(const Args a, const float *__restrict__ W,
     const StageRows emit{h, outs, ld, a.relu != 0, lane % LPR == 0, static_cast<unsigned short *>(a.Y), a.ld};
     constexpr int KF = LPR / 8;               // A fragments of a row: K <= 4 LPR, 32 k each
     for (int lb = static_cast<int>(blockIdx.x); lb < nblocks; lb += static_cast<int>(gridDim.x)) {
-        spmm_block<LPR, 4, kWaves, CP>(a, lb, 0, wave, emit);
+        spmm_block<LPR, 4, kWaves, MODE, MODE == kClasses, round_entries(MODE)>(a, lb, 0, wave, emit);
         __syncwarp();
         // the lane's MFMA coordinates, recomputed here (hidden from the optimiser) rather
         // than held in registers through the aggregation
@@ -666,13 +711,13 @@ int64_t schedule_blocks(Args &a) {
     return static_cast<int64_t>(a.nb_parts) + a.nb_dense + nb_sparse;
 }
 
-template <int LPR, bool CP>
+template <int LPR, int MODE>
 int launch_xw_window(Args a, const float *W, float *T, int32_t K, int32_t N, hipStream_t s) {
     const int64_t blocks = schedule_blocks<LPR>(a);
     if (blocks > 0x7FFFFFFF) return DUALGCN_ERR_UNSUPPORTED;
     if (blocks > 0) {
         const size_t lds = xw_lds_bytes(LPR, K, N);
-        const void *kern = reinterpret_cast<const void *>(&spmm_xw_kernel<LPR, CP>);
+        const void *kern = reinterpret_cast<const void *>(&spmm_xw_kernel<LPR, MODE>);
         if (lds > 64 * 1024) {
             const int st = hip_status(hipFuncSetAttribute(
                 kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
@@ -685,7 +730,7 @@ int launch_xw_window(Args a, const float *W, float *T, int32_t K, int32_t N, hip
         const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2048 / kThreads, (160 * 1024) / lds));
         const int64_t grid = std::min<int64_t>(
             blocks, std::max<int64_t>(per_cu * device_cus(), (blocks + kXwBlocksPerGroup - 1) / kXwBlocksPerGroup));
-        hipLaunchKernelGGL((spmm_xw_kernel<LPR, CP>), dim3(static_cast<unsigned>(grid)), dim3(kThreads),
+        hipLaunchKernelGGL((spmm_xw_kernel<LPR, MODE>), dim3(static_cast<unsigned>(grid)), dim3(kThreads),
                            lds, s, a, W, T, K, N, static_cast<int32_t>(blocks));
     }
     if (a.n_parts > 0)
@@ -694,17 +739,28 @@ int launch_xw_window(Args a, const float *W, float *T, int32_t K, int32_t N, hip
     return hip_status(hipGetLastError());
 }
 
-template <int LPR, int VEC, bool CP = false>
-int launch_window(Args a, bool bf, hipStream_t s) {
+template <int LPR, int VEC, int MODE>
+int launch_dual(Args a, bool bf, hipStream_t s) {
     const int64_t blocks = schedule_blocks<LPR>(a) * a.S;
     if (blocks == 0) return DUALGCN_OK;
     if (blocks > 0x7FFFFFFF) return DUALGCN_ERR_UNSUPPORTED;
     if (bf)
-        hipLaunchKernelGGL((spmm_dual_kernel<LPR, VEC, true, CP>), dim3(static_cast<unsigned>(blocks)),
+        hipLaunchKernelGGL((spmm_dual_kernel<LPR, VEC, true, MODE>), dim3(static_cast<unsigned>(blocks)),
                            dim3(kThreads), 0, s, a);
     else
-        hipLaunchKernelGGL((spmm_dual_kernel<LPR, VEC, false, CP>), dim3(static_cast<unsigned>(blocks)),
+        hipLaunchKernelGGL((spmm_dual_kernel<LPR, VEC, false, MODE>), dim3(static_cast<unsigned>(blocks)),
                            dim3(kThreads), 0, s, a);
+    return DUALGCN_OK;
+}
+
+template <int LPR, int VEC>
+int launch_window(Args a, int mode, bool bf, hipStream_t s) {
+    constexpr int CLS = LPR >= 8 && VEC == 4 ? kClasses : kBuffer;   // classes: rows of whole 128-byte lines
+    int st;
+    if (mode == kWide) st = launch_dual<LPR, VEC, kWide>(a, bf, s);
+    else if (mode == CLS) st = launch_dual<LPR, VEC, CLS>(a, bf, s);
+    else st = launch_dual<LPR, VEC, kBuffer>(a, bf, s);
+    if (st) return st;
     if (a.n_parts > 0) {
         if (bf)
             hipLaunchKernelGGL((combine_kernel<true>), dim3(static_cast<unsigned>(a.n_parts)),
@@ -759,17 +815,17 @@ int long_row_class(int lpr) {
 // the fused kernel rose from 22.5% to 26.8% and its fetched bytes fell from 28.6 to 27.0 GB.
 // Hot sets of 16 MiB or less, or a third class loading warm rows with sc0, were slower.
 //
-// gather_classes sets the class fields of `a` for gathers of w features of rows ld apart
-// and returns true when the launch should use them: the plan marked its cold columns, rows
-// are read whole with 16-byte loads, the operand fits the 32-bit offsets of a buffer load,
-// and it is larger than the memory-side cache.
-bool gather_classes(const Plan &p, int32_t ld, int32_t w, bool vec, Args &a) {
-    if (!vec || !p.cold_marked) return false;
+// gather_mode sets the buffer's size in `a` and picks the addressing for gathers of w features
+// of rows ld apart: 64-bit addresses when X is too large for a buffer load's 32-bit offsets;
+// classes when the plan marked its cold columns, rows are read whole with 16-byte loads, and X
+// is larger than the memory-side cache.
+int gather_mode(const Plan &p, int32_t ld, int32_t w, bool vec, Args &a) {
     const uint64_t bytes = static_cast<uint64_t>(p.n) * static_cast<uint64_t>(ld) * sizeof(float);
-    const uint64_t row_bytes = static_cast<uint64_t>(w) * sizeof(float);
-    if (bytes > 0xFFFFFFFFull || static_cast<uint64_t>(p.n) * row_bytes <= kGatherClassMinBytes) return false;
+    if (bytes > kMaxBufferBytes) return kWide;
     a.x_bytes = static_cast<uint32_t>(bytes);
-    return true;
+    const uint64_t row_bytes = static_cast<uint64_t>(w) * sizeof(float);
+    const bool classes = vec && p.cold_marked && static_cast<uint64_t>(p.n) * row_bytes > kGatherClassMinBytes;
+    return classes ? kClasses : kBuffer;
 }
 
 }  // namespace
@@ -820,16 +876,18 @@ int launch_spmm_xw(const Plan &p, const float *X, const float *W, float *T, void
     a.S = 1;
     const int lpr = window_lpr(F_in);
     a.n_long = p.n_long[long_row_class(lpr)];
-    const bool cp = gather_classes(p, F_in, F_in, true, a);
+    const int mode = gather_mode(p, F_in, F_in, true, a);
+    auto launch = [&](auto width) {
+        constexpr int LPR = decltype(width)::value;
+        if (mode == kWide) return launch_xw_window<LPR, kWide>(a, W, T, F_in, F_out, s);
+        if (mode == kClasses) return launch_xw_window<LPR, kClasses>(a, W, T, F_in, F_out, s);
+        return launch_xw_window<LPR, kBuffer>(a, W, T, F_in, F_out, s);
+    };
     int st = DUALGCN_ERR_UNSUPPORTED;
-    if (lpr == 8) st = cp ? launch_xw_window<8, true>(a, W, T, F_in, F_out, s)
-                          : launch_xw_window<8, false>(a, W, T, F_in, F_out, s);
-    else if (lpr == 16) st = cp ? launch_xw_window<16, true>(a, W, T, F_in, F_out, s)
-                                : launch_xw_window<16, false>(a, W, T, F_in, F_out, s);
-    else if (lpr == 32) st = cp ? launch_xw_window<32, true>(a, W, T, F_in, F_out, s)
-                                : launch_xw_window<32, false>(a, W, T, F_in, F_out, s);
-    else if (lpr == 64) st = cp ? launch_xw_window<64, true>(a, W, T, F_in, F_out, s)
-                                : launch_xw_window<64, false>(a, W, T, F_in, F_out, s);
+    if (lpr == 8) st = launch(std::integral_constant<int, 8>());
+    else if (lpr == 16) st = launch(std::integral_constant<int, 16>());
+    else if (lpr == 32) st = launch(std::integral_constant<int, 32>());
+    else if (lpr == 64) st = launch(std::integral_constant<int, 64>());
     if (st) return st;
     return note_use(p, s);
 }
@@ -852,18 +910,19 @@ int launch_spmm(const Plan &p, const float *X, void *Y, int32_t F, bool relu, bo
             a.S = 1;
             a.n_long = p.n_long[long_row_class(window_lpr(w))];
             // cache classes for the widths whose rows fill whole 128-byte lines
-            const bool cp = w > 16 && gather_classes(p, F, w, true, a);
-            if (w <= 4) st = launch_window<1, 4>(a, bf, s);
-            else if (w <= 8) st = launch_window<2, 4>(a, bf, s);
-            else if (w <= 16) st = launch_window<4, 4>(a, bf, s);
-            else if (w <= 32) st = cp ? launch_window<8, 4, true>(a, bf, s) : launch_window<8, 4>(a, bf, s);
-            else if (w <= 64) st = cp ? launch_window<16, 4, true>(a, bf, s) : launch_window<16, 4>(a, bf, s);
-            else if (w <= 128) st = cp ? launch_window<32, 4, true>(a, bf, s) : launch_window<32, 4>(a, bf, s);
-            else st = cp ? launch_window<64, 4, true>(a, bf, s) : launch_window<64, 4>(a, bf, s);
+            const int mode = gather_mode(p, F, w, w > 16, a);
+            if (w <= 4) st = launch_window<1, 4>(a, mode, bf, s);
+            else if (w <= 8) st = launch_window<2, 4>(a, mode, bf, s);
+            else if (w <= 16) st = launch_window<4, 4>(a, mode, bf, s);
+            else if (w <= 32) st = launch_window<8, 4>(a, mode, bf, s);
+            else if (w <= 64) st = launch_window<16, 4>(a, mode, bf, s);
+            else if (w <= 128) st = launch_window<32, 4>(a, mode, bf, s);
+            else st = launch_window<64, 4>(a, mode, bf, s);
         } else {
             // any other width or alignment: one feature per lane, 64-feature slices
             a.S = (w + 63) / 64;
-            st = launch_window<64, 1>(a, bf, s);
+            const int mode = gather_mode(p, F, w, false, a);
+            st = launch_window<64, 1>(a, mode, bf, s);
         }
     }
     if (st) return st;
