@@ -194,8 +194,8 @@ int dualgcn_plan_load(const dualgcn_csr *csr, const void *buf, size_t bytes, voi
  * X and Y are float32 row-major n x F, contiguous (leading dimension F), and
  * must not overlap.  Rows of the sparse region are computed by the sparse
  * path (runs of up to 8 short rows per lane group of a wavefront); rows of the
- * dense region by the dense path (a lane group per row under 512 entries -- 256,
- * 128, 64 for F <= 64, 32, 16 --, a wavefront per longer row; rows longer than the
+ * dense region by the dense path (a lane group per row under 256 entries --
+ * 128, 64 for F <= 32, 16 --, a wavefront per longer row; rows longer than the
  * dense chunk are split over
  * several wavefronts and combined in a fixed order).
  * Every row of Y is written, rows without entries with zeros.  Products are
@@ -476,9 +476,9 @@ typedef struct dualgcn_plan_info {
     int32_t n_split_rows;    /* dense rows longer than dense_chunk */
     int32_t n_split_parts;   /* wavefronts those rows are split over */
     int32_t n_tasks;         /* sparse-region tasks (runs of at most 8 short rows) */
-    int32_t n_long_rows;     /* dense rows of >= 512 entries (a wavefront each; the
-                                shorter dense rows get a lane group each; for F <= 64
-                                the bound is 256, for F <= 32 128, for F <= 16 64) */
+    int32_t n_long_rows;     /* dense rows of >= 512 entries (rows of >= 256 entries get a
+                                wavefront each, for F <= 32 from 128, for F <= 16 from 64;
+                                the shorter dense rows get a lane group each) */
     int32_t cold_marked;     /* 1 when the plan marks the columns outside the hottest
                                 65,536 (plans of more than 2^18 nodes): an SpMM whose
                                 operand is larger than 256 MiB and smaller than 4 GiB then

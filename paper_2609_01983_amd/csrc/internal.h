@@ -52,11 +52,12 @@ inline int32_t dense_chunk_for(int64_t nnz) {
 }
 // Widest feature window one SpMM launch covers; wider F is processed in windows.
 constexpr int kMaxSlice = 256;
-// Dense rows of at least 2^kLongRowOctave entries get a wavefront each; shorter dense
-// rows get one lane group each.  Narrow features mean small lane groups (more of them per
-// wavefront), so the SpMM lowers the bound by one octave per halving of the group below
-// 32 lanes, down to 2^(kLongRowOctave - kLongRowClasses + 1) entries: a group then never
-// walks more than 64 / (groups per wavefront) rounds of 16 entries alone.
+// Long dense rows get a wavefront each; shorter dense rows get one lane group each.  The
+// plan records where four bounds start in its order, 2^kLongRowOctave entries and one to
+// three octaves less.  The SpMM takes 256 entries for groups of 16 lanes and wider; narrow
+// features mean small lane groups (more of them per wavefront), so it lowers the bound by one
+// octave per halving of the group below 16 lanes, down to 64 entries: a group then
+// never walks more than 64 / (groups per wavefront) rounds of 16 entries alone.
 constexpr int kLongRowOctave = 9;
 constexpr int kLongRowClasses = 4;
 // A sparse-region task is a run of at most kTaskRows consecutive rows of the sorted

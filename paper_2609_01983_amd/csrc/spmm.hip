@@ -10,9 +10,9 @@
 //   parts      rows of the dense region longer than one chunk, split into parts
 //              of the plan's dense chunk (512 to 4096 entries, by the matrix's size;
 //              heaviest row first), one wavefront per part
-//   long       the other dense rows of at least 2^kLongRowOctave entries (one to
-//              three octaves fewer for groups narrower than 32 lanes), one
-//              wavefront per row, heaviest first
+//   long       the other dense rows of at least 256 entries (one or two octaves fewer
+//              for groups narrower than 16 lanes), one wavefront per row, heaviest
+//              first
 //   medium     the remaining dense rows, one lane group per row, heaviest first
 //   sparse     tasks of up to kTaskRows short consecutive rows, one lane group per
 //              task (the paper's "several rows per block")
@@ -21,19 +21,17 @@
 // features of a row: with VEC = 4 every lane makes one 16-byte load, so one
 // neighbour costs one coalesced load of the whole row (512 bytes = four 128-byte
 // lines at F = 128, 32 lanes).  Features beyond 256 are processed in windows of
-// 256; a window may be cut into S slices, workgroup b working on slice b % S
-// (used by the one-feature-per-lane path for arbitrary F).  Measured on c4/c5
-// (F = 128): cutting rows into 128-byte slices so that each XCD reads only its
-// own slice raises the L2 hit rate of a plain gather, but costs more in the SpMM
-// than it saves (every slice re-reads the indices and repeats the shuffles), so
-// rows are read whole.
+// 256; a window may be cut into S slices, workgroup b working on slice b % S (64 features
+// each where rows are whole lines, so that each XCD reads its own slices: sliced_window;
+// also the one-feature-per-lane path for arbitrary F).
 //
-// Gathers.  A group takes the entries of its row (or task) in rounds of R = 16 (12 on
-// large operands): each lane loads R / LPR (column, value) pairs with coalesced loads, the
-// pairs are broadcast inside the group with shuffles, and all R neighbour
-// slices are requested before the first product, so every group keeps R
-// loads in flight (the ILP of the paper's dense path, Alg. 1, deepened).  Nothing in a round
-// branches (see gather), and the next round's pairs are requested with this round's slices.
+// Gathers.  A group takes the entries of its row (or task) in rounds of 16:
+// each lane loads 16 / LPR (column, value) pairs with coalesced loads, the
+// pairs are broadcast inside the group with shuffles, and all 16 neighbour
+// slices (eight on large operands) are requested before the first product, so every group
+// keeps that many loads in flight (the ILP of the paper's dense path, Alg. 1, deepened).
+// Nothing in a round branches (see gather), and the next round's pairs are requested with this
+// round's slices.
 // On large operands the rows of cold columns (marked by the plan) are read non-temporally
 // (the cache classes below).  Before the rounds were free of branches a lone wavefront took
 // 1.65 us a round (F = 128) and the launches on small and middling graphs were bound by that
@@ -43,8 +41,8 @@
 //
 // Dense path (paper: one row per block, 4-way ILP and a shared reduction): a long
 // row gets a wavefront whose groups take rounds of the row in turn and are summed
-// with a butterfly over the lanes; a dense row shorter than 2^kLongRowOctave
-// entries gets one lane group, which fills its rounds better (measured: the SBM
+// with a butterfly over the lanes; a dense row shorter than the long rows' bound
+// gets one lane group, which fills its rounds better (measured: the SBM
 // workload's dense rows of 100-250 entries run 9% faster than with a wavefront).
 // A split row's parts each write a float64 partial, and a small second kernel
 // sums them in part order and writes the row.  The kernel boundary makes the
@@ -53,7 +51,7 @@
 // Y is bit-reproducible.
 //
 // Sparse path (tasks): the group walks the task's entries as one stream, so even
-// rows with one or two entries share a round of R gathers; a row is written
+// rows with one or two entries share a round of gathers; a row is written
 // as soon as its last entry has been added.
 //
 // Summation: products and the sum of one round (<= 16 terms) are float32,
@@ -69,13 +67,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-// Entries a lane group gathers per round.  Operands larger than the memory-side cache take 12:
-// what 16 wavefronts per CU then have in flight (6 MiB per XCD) pushes less out of the 4 MiB L2.
-// Measured on R-MAT n = 2^21 and 2^22, F = 64, branch-free gathers: 16 per round 1.70 and 2.06
-// ms, 12 per round 1.69 and 2.03, 8 per round 1.71 and 2.05; smaller operands are faster
-// with 16 (block model n = 2^18, F = 128: 0.450 against 0.460 ms).
-constexpr int kRound = 16;
-constexpr int kRoundLarge = 12;
+constexpr int kRound = 16;            // entries a lane group adds per round
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -146,6 +138,7 @@ struct Args {
     int32_t f0;                 // first feature of this launch window
     int32_t fend;               // end of the valid features of the window
     int32_t S;                  // feature slices in the window
+    int32_t sw;                 // features per slice (at most those of a lane group)
     int32_t nb_parts;           // logical workgroups of hub-row parts
     int32_t nb_long;            // logical workgroups of long dense rows (a wavefront each)
     int32_t nb_dense;           // nb_long + those of the other dense rows (a group each)
@@ -215,12 +208,24 @@ struct StageRows {
 constexpr int kCpolNt = 2;                    // the nt field of a gfx950 buffer load
 constexpr uint32_t kRowMask = 0x7FFFFFFFu;
 
-// How a launch's gathers address X.  kBuffer: buffer loads at 32-bit byte offsets (X up to
-// kMaxBufferBytes); kClasses: the same with the cache classes above; kWide: 64-bit addresses.
-enum GatherMode { kBuffer = 0, kClasses = 1, kWide = 2 };
-constexpr int round_entries(int mode) {
-    return mode == kBuffer ? kRound : kRoundLarge;
-}
+// How a launch's gathers address X, and how many are requested at a time.
+//   kBuffer   buffer loads at 32-bit byte offsets (X up to kMaxBufferBytes), a round of 16
+//   kHalves   the same, half a round, for operands that only the memory-side cache holds
+//   kClasses  the same as kHalves with the cache classes above, for larger operands
+//   kWide     64-bit addresses, half a round
+// A round at once puts 8 MiB of requested lines per XCD in flight (16 wavefronts a CU), twice
+// its L2, and each request takes the place of a line: half a round hides the latency as well
+// once the operand misses the L2 anyway.  Measured on R-MAT graphs, a round / half (us):
+// classes F = 64, n = 2^22 2060 / 2030, n = 2^21 1709 / 1681; F = 128, n = 2^22 4073 / 4046;
+// the fused kernel 128 -> 64, n = 2^22 3980 / 3944.  Operands of 128 to 256 MiB, F = 64: n =
+// 2^20 437 / 425, 700,000 (17.5M entries) 406 / 397; below, a round wins (n = 2^19 190 / 197;
+// block model n = 2^18, F = 128 424 / 458).  The sums are the same either way.
+enum GatherMode { kBuffer = 0, kClasses = 1, kWide = 2, kHalves = 3 };
+
+// Dynamic LDS that keeps a CU to four workgroups where the registers would let five in
+// (kHalves: n = 2^20, F = 64 433 us with five, 425 with four; kWide, n = 2^22, F = 256: 9160
+// and 8968).
+constexpr unsigned kFourGroupsLds = 38 * 1024;
 
 // Offset of an entry that reads nothing: past the end of every buffer, also with a lane's
 // offset inside a window (below 1 KiB) added, so that a buffer load of it returns zeros.
@@ -228,12 +233,15 @@ constexpr uint32_t kNoEntry = 0xFFFFF000u;
 constexpr uint64_t kMaxBufferBytes = kNoEntry;
 constexpr uint32_t kNoRow = 0x80000000u;        // marks an invalid entry's row in kWide
 
-// Entries [e, min(e + R, e_end)) of the sorted copy (e_end > 0), as seen by lane li of a
-// group: lane li loads entries e + li + k LPR; entry u is then held by lane u % LPR in
+// Entries [e, min(e + kRound, e_end)) of the sorted copy (e_end > 0), as seen by lane li of
+// a group: lane li loads entries e + li + k LPR; entry u is then held by lane u % LPR in
 // register u / LPR.  The loads are unconditional (past the end they read the last entry).
-template <int LPR, int R>
+// ready() turns the columns into what the gathers broadcast: byte offsets into X (one multiply
+// per entry instead of one per lane and entry), or rows in kWide; an entry past the end gets
+// weight zero and an offset that reads zeros.
+template <int LPR, int MODE>
 struct Round {
-    static constexpr int EPL = (R + LPR - 1) / LPR;   // entries per lane
+    static constexpr int EPL = (kRound + LPR - 1) / LPR;   // entries per lane
     int32_t c[EPL];
     float v[EPL];
 
@@ -243,6 +251,24 @@ struct Round {
             const int32_t idx = min(e + li + k * LPR, e_end - 1);
             c[k] = a.pcol[idx];
             v[k] = a.pval[idx];
+        }
+    }
+
+    __device__ __forceinline__ void ready(const Args &a, int32_t e, int32_t e_end, int li) {
+#pragma unroll
+        for (int k = 0; k < EPL; ++k) {
+            const bool ok = li + k * LPR < kRound && e + li + k * LPR < e_end;
+            v[k] = ok ? v[k] : 0.f;
+            const uint32_t row = static_cast<uint32_t>(c[k]) & kRowMask;
+            uint32_t at;
+            if constexpr (MODE == kWide) {
+                at = ok ? row : row | kNoRow;
+            } else {
+                at = row * (static_cast<uint32_t>(a.ld) * 4u);
+                if constexpr (MODE == kClasses) at |= static_cast<uint32_t>(c[k]) >> 31;   // a marked (cold) column
+                at = ok ? at : kNoEntry;
+            }
+            c[k] = static_cast<int32_t>(at);
         }
     }
 };
@@ -259,46 +285,26 @@ __device__ __forceinline__ void load_x_buf(__amdgpu_buffer_rsrc_t rx, uint32_t o
     }
 }
 
-// Requests the R neighbour slices of a round (invalid entries read nothing and get
-// weight zero).
+// Requests the neighbour slices of entries U0 .. U0 + Q - 1 of a round (ready() done).
 // The broadcasts read lane gbase + u % LPR with ds_bpermute: the group's base byte
 // address is hidden from the optimiser, so that the constant u % LPR lanes go into the
 // instruction's offset field instead of one precomputed address register per u
 // (sixteen registers held through the whole kernel otherwise).
-// The buffer modes broadcast byte offsets (one multiply per entry instead of one per lane and
-// entry), and an entry past the end is an offset past the buffer instead of a branch: with a
-// branch per gather the compiler waited for the first gather inside its branch and for
-// every broadcast before the next one, so a round took two memory latencies and sixteen
-// LDS latencies (1.65 us on an idle chip, F = 128).
-template <int LPR, int VEC, int MODE, int R>
-__device__ __forceinline__ void gather(const Args &a, const Round<LPR, R> &r, int32_t e, int32_t e_end, int li,
-                                       int gbase, int f, bool fin, float (&as)[R],
-                                       float (&xs)[R][VEC]) {
+// No branches: with a branch per gather the compiler waited for the first gather inside its
+// branch and for every broadcast before the next one, so a round took two memory latencies
+// and sixteen LDS latencies (1.65 us on an idle chip, F = 128).
+template <int LPR, int VEC, int MODE, int U0, int Q>
+__device__ __forceinline__ void gather(const Args &a, const Round<LPR, MODE> &r, int gbase, int f, bool fin,
+                                       float (&as)[Q], float (&xs)[Q][VEC]) {
     static_assert(MODE != kClasses || VEC == 4, "cache classes need 16-byte loads");
     int base4 = gbase * 4;
     asm volatile("" : "+v"(base4));
-    constexpr int EPL = Round<LPR, R>::EPL;
-    uint32_t o[EPL];
-    float v[EPL];
-#pragma unroll
-    for (int k = 0; k < EPL; ++k) {
-        const bool ok = li + k * LPR < R && e + li + k * LPR < e_end;
-        v[k] = ok ? r.v[k] : 0.f;
-        const uint32_t row = static_cast<uint32_t>(r.c[k]) & kRowMask;
-        if constexpr (MODE == kWide) {
-            o[k] = ok ? row : row | kNoRow;
-        } else {
-            uint32_t at = row * (static_cast<uint32_t>(a.ld) * 4u);
-            if constexpr (MODE == kClasses) at |= static_cast<uint32_t>(r.c[k]) >> 31;   // a marked (cold) column
-            o[k] = ok ? at : kNoEntry;
-        }
-    }
     if constexpr (MODE == kWide) {
 #pragma unroll
-        for (int u = 0; u < R; ++u) {
-            const int src = base4 + (u % LPR) * 4;
-            const uint32_t row = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, static_cast<int>(o[u / LPR])));
-            as[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(v[u / LPR])));
+        for (int u = 0; u < Q; ++u) {
+            const int src = base4 + ((U0 + u) % LPR) * 4;
+            const uint32_t row = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, r.c[(U0 + u) / LPR]));
+            as[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(r.v[(U0 + u) / LPR])));
             // an invalid entry reads the row of the last one and drops it
             const bool ok = (row & kNoRow) == 0;
             load_x<VEC>(a.X + static_cast<int64_t>(row & kRowMask) * a.ld + (fin ? f : a.f0), xs[u]);
@@ -312,11 +318,11 @@ __device__ __forceinline__ void gather(const Args &a, const Round<LPR, R> &r, in
             const_cast<float *>(a.X) + a.f0, 0, static_cast<int>(a.x_bytes - static_cast<uint32_t>(a.f0) * 4u), 0x00020000);
         const uint32_t lane_off = fin ? static_cast<uint32_t>(f - a.f0) * 4u : 0u;
 #pragma unroll
-        for (int u = 0; u < R; ++u) {
-            const int src = base4 + (u % LPR) * 4;
-            const uint32_t at = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, static_cast<int>(o[u / LPR])));
-            as[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(v[u / LPR])));
-            if constexpr (MODE == kBuffer) {
+        for (int u = 0; u < Q; ++u) {
+            const int src = base4 + ((U0 + u) % LPR) * 4;
+            const uint32_t at = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, r.c[(U0 + u) / LPR]));
+            as[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(r.v[(U0 + u) / LPR])));
+            if constexpr (MODE != kClasses) {
                 load_x_buf<VEC, 0>(rx, at + lane_off, xs[u]);
             } else {
                 const uint32_t off = (at & ~1u) + lane_off;
@@ -327,39 +333,98 @@ __device__ __forceinline__ void gather(const Args &a, const Round<LPR, R> &r, in
     }
 }
 
-// Dense path: one lane group accumulates the rounds of 16 entries at e0, e0 + STEP, ...
-// below e1 of one row into tot.  With PF the next round's columns and values are requested
-// behind the current round's gathers, so that a round waits for one memory latency, not two.
-template <int LPR, int VEC, int MODE, bool PF, int R>
-__device__ __forceinline__ void dense_rounds(const Args &a, int32_t e0, int32_t e1, int32_t step, int li,
-                                             int gbase, int f, bool fin, double (&tot)[VEC]) {
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) tot[j] = 0.0;
+// A lane group's walk over the rounds of kRound entries at e0, e0 + step, ... below e1:
+// term(e, weight, slice) for every entry in order (entries past e1 come with weight and
+// slice zero), flush() after every round.  The next round's columns and values are requested
+// behind the current round's gathers (not for groups of one or two lanes, which hold 16 or 8
+// of them in registers: a wavefront less per SIMD).
+template <int LPR, int VEC, int MODE, class Term, class Flush>
+__device__ __forceinline__ void walk_rounds(const Args &a, int32_t e0, int32_t e1, int32_t step, int li,
+                                            int gbase, int f, bool fin, const Term &term, const Flush &flush) {
     if (e0 >= e1) return;
-    Round<LPR, R> r;
+    constexpr int Q = MODE == kBuffer ? kRound : kRound / 2;   // gathers requested at a time
+    constexpr bool PF = LPR >= 4;
+    Round<LPR, MODE> r;
     if constexpr (PF) r.load(a, e0, e1, li);
     for (int32_t e = e0; e < e1; e += step) {
         if constexpr (!PF) r.load(a, e, e1, li);
-        float as[R], xs[R][VEC];
-        gather<LPR, VEC, MODE, R>(a, r, e, e1, li, gbase, f, fin, as, xs);
-        if constexpr (PF) r.load(a, e + step, e1, li);
-        float acc[VEC];
+        r.ready(a, e, e1, li);
+        if constexpr (Q == kRound) {
+            float as[Q], xs[Q][VEC];
+            gather<LPR, VEC, MODE, 0, Q>(a, r, gbase, f, fin, as, xs);
+            if constexpr (PF) r.load(a, e + step, e1, li);
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
+            for (int u = 0; u < Q; ++u) term(e + u, as[u], xs[u]);
+        } else {
+            {
+                float as[Q], xs[Q][VEC];
+                gather<LPR, VEC, MODE, 0, Q>(a, r, gbase, f, fin, as, xs);
 #pragma unroll
-        for (int u = 0; u < R; ++u)
+                for (int u = 0; u < Q; ++u) term(e + u, as[u], xs[u]);
+            }
+            __builtin_amdgcn_sched_barrier(0);       // the second half's gathers stay behind
+            if (e + Q < e1) {
+                float as[Q], xs[Q][VEC];
+                gather<LPR, VEC, MODE, Q, Q>(a, r, gbase, f, fin, as, xs);
+                if constexpr (PF) r.load(a, e + step, e1, li);
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) acc[j] = fmaf(as[u], xs[u][j], acc[j]);
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) tot[j] += static_cast<double>(acc[j]);
+                for (int u = 0; u < Q; ++u) term(e + Q + u, as[u], xs[u]);
+            }
+        }
+        flush();
     }
 }
 
-// The wavefront's groups summed by a butterfly: every lane then holds the sums of its features.
-template <int LPR, int VEC>
-__device__ __forceinline__ void sum_groups(double (&tot)[VEC]) {
+// Dense path: a lane group's sums over its rounds of one row, in V chains (round q of the
+// group adds to chain q % V, by rotating them) that are then added pairwise: as (0 + 2) +
+// (1 + 3) for four, whichever chain is first after the last rotation.
+template <int LPR, int VEC, int MODE, int V>
+__device__ __forceinline__ void dense_rounds(const Args &a, int32_t e0, int32_t e1, int32_t step, int li,
+                                             int gbase, int f, bool fin, double (&tot)[VEC]) {
+    float acc[VEC];
+    double chain[V][VEC];
 #pragma unroll
-    for (int m = LPR; m < 64; m <<= 1)
+    for (int j = 0; j < VEC; ++j) {
+        acc[j] = 0.f;
+#pragma unroll
+        for (int q = 0; q < V; ++q) chain[q][j] = 0.0;
+    }
+    walk_rounds<LPR, VEC, MODE>(
+        a, e0, e1, step, li, gbase, f, fin,
+        [&](int32_t, float w, const float (&x)[VEC]) {
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) acc[j] = fmaf(w, x[j], acc[j]);
+        },
+        [&]() {
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                const double first = chain[0][j] + static_cast<double>(acc[j]);
+#pragma unroll
+                for (int q = 0; q + 1 < V; ++q) chain[q][j] = chain[q + 1][j];
+                chain[V - 1][j] = first;
+                acc[j] = 0.f;
+            }
+        });
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) {
+        if constexpr (V == 1) tot[j] = chain[0][j];
+        else if constexpr (V == 2) tot[j] = chain[0][j] + chain[1][j];
+        else tot[j] = (chain[0][j] + chain[2][j]) + (chain[1][j] + chain[3][j]);
+    }
+}
+
+// Entries [e0, e1) of one row by a wavefront: its groups take rounds in turn and a butterfly
+// adds their sums; every lane then holds the sums of its features.  The rounds form four
+// chains (every fourth round), whatever the group's width: four 16-lane groups have one each,
+// wider groups two or four.  So the SpMM's slices of 64 features and the fused kernel, which
+// reads rows whole, add a long row in the same order and give the same bits.
+template <int LPR, int VEC, int MODE>
+__device__ __forceinline__ void long_row(const Args &a, int32_t e0, int32_t e1, int li, int gw, int gbase,
+                                         int f, bool fin, double (&tot)[VEC]) {
+    constexpr int V = VEC == 4 && LPR > 16 ? LPR / 16 : 1;
+    dense_rounds<LPR, VEC, MODE, V>(a, e0 + gw * kRound, e1, 64 / LPR * kRound, li, gbase, f, fin, tot);
+#pragma unroll
+    for (int m = 32; m >= LPR; m >>= 1)
 #pragma unroll
         for (int j = 0; j < VEC; ++j) tot[j] += __shfl_xor(tot[j], m, 64);
 }
@@ -376,19 +441,18 @@ __device__ __forceinline__ int32_t task_meta(const int32_t (&m)[N], int j, int g
 
 // The work of logical workgroup lb (feature slice `slice`) for wavefront `wave` of a
 // workgroup of WAVES wavefronts; finished rows go to `emit`.
-template <int LPR, int VEC, int WAVES, int MODE, bool PF, int R, class Emit>
+template <int LPR, int VEC, int WAVES, int MODE, class Emit>
 __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int wave,
                                            const Emit &emit) {
     constexpr int GPW = 64 / LPR;                 // lane groups per wavefront
-    constexpr int SW = LPR * VEC;                 // features per slice
     constexpr int RPL = (kTaskRows + LPR - 1) / LPR;
 
     const int lane = static_cast<int>(threadIdx.x) & 63;
     const int li = lane % LPR;
     const int gw = lane / LPR;
     const int gbase = lane - li;
-    const int f = a.f0 + slice * SW + li * VEC;
-    const bool fin = f < a.fend;
+    const int f = a.f0 + slice * a.sw + li * VEC;
+    const bool fin = li * VEC < a.sw && f < a.fend;
 
     if (lb >= a.nb_parts + a.nb_long && lb < a.nb_parts + a.nb_dense) {
         // ---------------- dense path, shorter rows: one lane group per row
@@ -396,7 +460,7 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
         const int64_t i = a.n - a.n_long - 1 - gi;
         if (i < a.n_sparse) return;           // the whole group leaves together
         double tot[VEC];
-        dense_rounds<LPR, VEC, MODE, PF, R>(a, a.pptr[i], a.pptr[i + 1], R, li, gbase, f, fin, tot);
+        dense_rounds<LPR, VEC, MODE, 1>(a, a.pptr[i], a.pptr[i + 1], kRound, li, gbase, f, fin, tot);
         emit.row(a.perm[i], gw * kTaskRows, tot, f, fin);
         return;
     }
@@ -421,8 +485,7 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
             if (e1 - e0 > a.dense_chunk) return;   // covered by its parts
         }
         double tot[VEC];
-        dense_rounds<LPR, VEC, MODE, PF, R>(a, e0 + gw * R, e1, GPW * R, li, gbase, f, fin, tot);
-        sum_groups<LPR, VEC>(tot);
+        long_row<LPR, VEC, MODE>(a, e0, e1, li, gw, gbase, f, fin, tot);
         if (part < 0) {
             if (gw == 0) emit.row(a.perm[i], 0, tot, f, fin);
             return;
@@ -467,18 +530,12 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
         tot[j] = 0.0;
         part[j] = 0.f;
     }
-    Round<LPR, R> r;
-    if constexpr (PF) r.load(a, e_begin, e_end, li);
-    for (int32_t e = e_begin; e < e_end; e += R) {
-        if constexpr (!PF) r.load(a, e, e_end, li);
-        float as[R], xs[R][VEC];
-        gather<LPR, VEC, MODE, R>(a, r, e, e_end, li, gbase, f, fin, as, xs);
-        if constexpr (PF) r.load(a, e + R, e_end, li);
+    walk_rounds<LPR, VEC, MODE>(
+        a, e_begin, e_end, kRound, li, gbase, f, fin,
+        [&](int32_t e, float w, const float (&x)[VEC]) {
 #pragma unroll
-        for (int u = 0; u < R; ++u) {
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) part[j] = fmaf(as[u], xs[u][j], part[j]);
-            if (e + u + 1 == cur_end) {       // the current row ends with this entry
+            for (int j = 0; j < VEC; ++j) part[j] = fmaf(w, x[j], part[j]);
+            if (e + 1 == cur_end) {           // the current row ends with this entry
 #pragma unroll
                 for (int j = 0; j < VEC; ++j) {
                     tot[j] += static_cast<double>(part[j]);
@@ -492,19 +549,20 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
                     cur_out = task_meta<LPR>(rout, cur, gbase);
                 }
             }
-        }
+        },
+        [&]() {
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) {
-            tot[j] += static_cast<double>(part[j]);
-            part[j] = 0.f;
-        }
-    }
+            for (int j = 0; j < VEC; ++j) {
+                tot[j] += static_cast<double>(part[j]);
+                part[j] = 0.f;
+            }
+        });
 }
 
 template <int LPR, int VEC, bool BF, int MODE>
 __global__ __launch_bounds__(kThreads) void spmm_dual_kernel(const Args a) {
     const StoreRows<VEC, BF> emit{a.Y, a.ld, a.relu != 0};
-    spmm_block<LPR, VEC, kWaves, MODE, MODE == kBuffer && LPR >= 4, round_entries(MODE)>(
+    spmm_block<LPR, VEC, kWaves, MODE>(
         a, static_cast<int>(blockIdx.x) / a.S, static_cast<int>(blockIdx.x) % a.S,
         static_cast<int>(threadIdx.x) >> 6, emit);
 }
@@ -601,7 +659,7 @@ void spmm_xw_kernel(const Args a, const float *__restrict__ W,
     const StageRows emit{h, outs, ld, a.relu != 0, lane % LPR == 0, static_cast<unsigned short *>(a.Y), a.ld};
     constexpr int KF = LPR / 8;               // A fragments of a row: K <= 4 LPR, 32 k each
     for (int lb = static_cast<int>(blockIdx.x); lb < nblocks; lb += static_cast<int>(gridDim.x)) {
-        spmm_block<LPR, 4, kWaves, MODE, MODE == kClasses, round_entries(MODE)>(a, lb, 0, wave, emit);
+        spmm_block<LPR, 4, kWaves, MODE>(a, lb, 0, wave, emit);
         __syncwarp();
         // the lane's MFMA coordinates, recomputed here (hidden from the optimiser) rather
         // than held in registers through the aggregation
@@ -742,14 +800,15 @@ int launch_xw_window(Args a, const float *W, float *T, int32_t K, int32_t N, hip
 template <int LPR, int VEC, int MODE>
 int launch_dual(Args a, bool bf, hipStream_t s) {
     const int64_t blocks = schedule_blocks<LPR>(a) * a.S;
+    constexpr unsigned lds = MODE == kHalves || MODE == kWide ? kFourGroupsLds : 0;
     if (blocks == 0) return DUALGCN_OK;
     if (blocks > 0x7FFFFFFF) return DUALGCN_ERR_UNSUPPORTED;
     if (bf)
         hipLaunchKernelGGL((spmm_dual_kernel<LPR, VEC, true, MODE>), dim3(static_cast<unsigned>(blocks)),
-                           dim3(kThreads), 0, s, a);
+                           dim3(kThreads), lds, s, a);
     else
         hipLaunchKernelGGL((spmm_dual_kernel<LPR, VEC, false, MODE>), dim3(static_cast<unsigned>(blocks)),
-                           dim3(kThreads), 0, s, a);
+                           dim3(kThreads), lds, s, a);
     return DUALGCN_OK;
 }
 
@@ -758,6 +817,7 @@ int launch_window(Args a, int mode, bool bf, hipStream_t s) {
     constexpr int CLS = LPR >= 8 && VEC == 4 ? kClasses : kBuffer;   // classes: rows of whole 128-byte lines
     int st;
     if (mode == kWide) st = launch_dual<LPR, VEC, kWide>(a, bf, s);
+    else if (mode == kHalves && LPR == 16) st = launch_dual<LPR, VEC, LPR == 16 ? kHalves : kBuffer>(a, bf, s);
     else if (mode == CLS) st = launch_dual<LPR, VEC, CLS>(a, bf, s);
     else st = launch_dual<LPR, VEC, kBuffer>(a, bf, s);
     if (st) return st;
@@ -800,10 +860,31 @@ int window_lpr(int32_t w) {
     return w <= 4 ? 1 : w <= 8 ? 2 : w <= 16 ? 4 : w <= 32 ? 8 : w <= 64 ? 16 : w <= 128 ? 32 : 64;
 }
 
-int long_row_class(int lpr) {
-    int cls = 0;
-    for (int g = lpr; g < 32 && cls < kLongRowClasses - 1; g *= 2) ++cls;
+// Rows of at least 2^(kLongRowOctave - class) entries get a wavefront: class 1 (256 entries) for
+// groups of 16 lanes and wider, an octave less per halving below; class 0 where the launch is
+// bound by the memory fabric and rows are wider than 64 features (fused kernel 128 -> 64, n =
+// 2^22: 3944 us against 4038, each long row being a 16-row matrix tile of its own there).
+// The rule goes by the launch's shape and never by the group's width, so that the fused kernel
+// and the SpMM split a row alike.
+int long_row_class(int lpr, int mode, int32_t w) {
+    int cls = (mode == kClasses || mode == kWide) && w > 64 ? 0 : 1;
+    for (int g = lpr; g < 16 && cls < kLongRowClasses - 1; g *= 2) ++cls;
     return cls;
+}
+
+// A window of 128, 192 or 256 features whose rows are whole 128-byte lines is cut into slices
+// of 64 features, and workgroup b takes slice b % S: workgroups go to the XCDs in turn, so
+// an XCD reads every second (or fourth) 256-byte piece of the rows and its 4 MiB L2 keeps twice
+// (four times) as many of the hottest rows.  Each slice reads the columns and values again
+// (8 bytes an entry against 256 gathered).  Measured, whole rows and slices of 64 (us):
+//   F = 128  block model n = 2^18 448 / 424, R-MAT n = 2^19 426 / 376, 1.5M 1031 / 967,
+//            n = 2^21 3475 / 3331, n = 2^22 4201 / 4059
+//   F = 256  n = 2^19 1036 / 860, 1.5M 2315 / 2048, n = 2^21 7891 / 7053
+// Slices of 32 features, whose wavefronts walk eight rows side by side, lose it again (F = 128,
+// n = 2^22: 4542).  Where slices would share lines or leave lanes idle whole rows win (1.5M
+// nodes, F = 96 788 / 929, F = 100 1048 / 1492, F = 160 1371 / 1592, F = 200 1949 / 2531).
+bool sliced_window(int32_t ld, int32_t w) {
+    return w > 64 && w % 64 == 0 && ld % 32 == 0;
 }
 
 // Cache classes of a launch's gathers (the plan marks every column outside the hottest
@@ -818,14 +899,14 @@ int long_row_class(int lpr) {
 // gather_mode sets the buffer's size in `a` and picks the addressing for gathers of w features
 // of rows ld apart: 64-bit addresses when X is too large for a buffer load's 32-bit offsets;
 // classes when the plan marked its cold columns, rows are read whole with 16-byte loads, and X
-// is larger than the memory-side cache.
+// is larger than the memory-side cache; half rounds when it is larger than half that cache.
 int gather_mode(const Plan &p, int32_t ld, int32_t w, bool vec, Args &a) {
     const uint64_t bytes = static_cast<uint64_t>(p.n) * static_cast<uint64_t>(ld) * sizeof(float);
     if (bytes > kMaxBufferBytes) return kWide;
     a.x_bytes = static_cast<uint32_t>(bytes);
-    const uint64_t row_bytes = static_cast<uint64_t>(w) * sizeof(float);
-    const bool classes = vec && p.cold_marked && static_cast<uint64_t>(p.n) * row_bytes > kGatherClassMinBytes;
-    return classes ? kClasses : kBuffer;
+    if (!vec || !p.cold_marked) return kBuffer;
+    const uint64_t operand = static_cast<uint64_t>(p.n) * static_cast<uint64_t>(w) * sizeof(float);
+    return operand > kGatherClassMinBytes ? kClasses : operand > kGatherClassMinBytes / 2 ? kHalves : kBuffer;
 }
 
 }  // namespace
@@ -874,9 +955,10 @@ int launch_spmm_xw(const Plan &p, const float *X, const float *W, float *T, void
     a.f0 = 0;
     a.fend = F_in;
     a.S = 1;
+    a.sw = F_in;
     const int lpr = window_lpr(F_in);
-    a.n_long = p.n_long[long_row_class(lpr)];
     const int mode = gather_mode(p, F_in, F_in, true, a);
+    a.n_long = p.n_long[long_row_class(lpr, mode, F_in)];
     auto launch = [&](auto width) {
         constexpr int LPR = decltype(width)::value;
         if (mode == kWide) return launch_xw_window<LPR, kWide>(a, W, T, F_in, F_out, s);
@@ -905,21 +987,24 @@ int launch_spmm(const Plan &p, const float *X, void *Y, int32_t F, bool relu, bo
         a.f0 = f0;
         a.fend = f0 + w;
         if (vec) {
-            // whole rows: the smallest power-of-two lane group with 4 features per lane;
-            // groups under 32 lanes hand rows from a lower length bound to wavefronts
-            a.S = 1;
-            a.n_long = p.n_long[long_row_class(window_lpr(w))];
+            // the smallest power-of-two lane group with 4 features per lane that holds the
+            // window, or slices of 64 features (see sliced_window)
+            const int lpr = sliced_window(F, w) ? 16 : window_lpr(w);
+            a.sw = 4 * lpr;
+            a.S = (w + a.sw - 1) / a.sw;
             // cache classes for the widths whose rows fill whole 128-byte lines
             const int mode = gather_mode(p, F, w, w > 16, a);
-            if (w <= 4) st = launch_window<1, 4>(a, mode, bf, s);
-            else if (w <= 8) st = launch_window<2, 4>(a, mode, bf, s);
-            else if (w <= 16) st = launch_window<4, 4>(a, mode, bf, s);
-            else if (w <= 32) st = launch_window<8, 4>(a, mode, bf, s);
-            else if (w <= 64) st = launch_window<16, 4>(a, mode, bf, s);
-            else if (w <= 128) st = launch_window<32, 4>(a, mode, bf, s);
+            a.n_long = p.n_long[long_row_class(lpr, mode, w)];
+            if (lpr == 1) st = launch_window<1, 4>(a, mode, bf, s);
+            else if (lpr == 2) st = launch_window<2, 4>(a, mode, bf, s);
+            else if (lpr == 4) st = launch_window<4, 4>(a, mode, bf, s);
+            else if (lpr == 8) st = launch_window<8, 4>(a, mode, bf, s);
+            else if (lpr == 16) st = launch_window<16, 4>(a, mode, bf, s);
+            else if (lpr == 32) st = launch_window<32, 4>(a, mode, bf, s);
             else st = launch_window<64, 4>(a, mode, bf, s);
         } else {
             // any other width or alignment: one feature per lane, 64-feature slices
+            a.sw = 64;
             a.S = (w + 63) / 64;
             const int mode = gather_mode(p, F, w, false, a);
             st = launch_window<64, 1>(a, mode, bf, s);
