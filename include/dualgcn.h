@@ -196,8 +196,9 @@ int dualgcn_plan_load(const dualgcn_csr *csr, const void *buf, size_t bytes, voi
  * path (runs of up to 8 short rows per lane group of a wavefront); rows of the
  * dense region by the dense path (a lane group per row under 256 entries --
  * 128, 64 for F <= 32, 16 --, a wavefront per longer row; rows longer than the
- * dense chunk are split over
- * several wavefronts and combined in a fixed order).
+ * dense chunk are split over several wavefronts and combined in a fixed order; when rows
+ * of at least 512 entries and those parts are no more than the compute units, a workgroup
+ * takes each).
  * Every row of Y is written, rows without entries with zeros.  Products are
  * float32; sums are formed in float32 over at most 16 terms and then in
  * float64, and each output is rounded once to float32, so results do not

@@ -12,7 +12,8 @@
 //              heaviest row first), one wavefront per part
 //   long       the other dense rows of at least 256 entries (one or two octaves fewer
 //              for groups narrower than 16 lanes), one wavefront per row, heaviest
-//              first
+//              first; where parts and rows of at least 512 entries are no more than the
+//              CUs, a workgroup each
 //   medium     the remaining dense rows, one lane group per row, heaviest first
 //   sparse     tasks of up to kTaskRows short consecutive rows, one lane group per
 //              task (the paper's "several rows per block")
@@ -133,6 +134,8 @@ struct Args {
     void *Y;                    // float32, or bfloat16 when the kernel's BF is set (fused: H or null)
     uint32_t x_bytes;           // bytes of X that gathers may read (cache-class loads)
     int32_t n, n_sparse, n_tasks, n_parts, n_long;
+    int32_t n_coop;             // rows of at least 2^kLongRowOctave entries that share workgroups, or 0
+    int32_t coop;               // parts and those rows are a workgroup's each (see shares_rows)
     int32_t dense_chunk;        // entries per part of a split dense row (the plan's)
     int32_t ld;                 // leading dimension of X and Y (= F)
     int32_t f0;                 // first feature of this launch window
@@ -140,7 +143,8 @@ struct Args {
     int32_t S;                  // feature slices in the window
     int32_t sw;                 // features per slice (at most those of a lane group)
     int32_t nb_parts;           // logical workgroups of hub-row parts
-    int32_t nb_long;            // logical workgroups of long dense rows (a wavefront each)
+    int32_t nb_coop;            // logical workgroups of the longest dense rows (one each; 0: no sharing)
+    int32_t nb_long;            // nb_coop + those of the other long dense rows (a wavefront each)
     int32_t nb_dense;           // nb_long + those of the other dense rows (a group each)
     int32_t relu;
 };
@@ -222,9 +226,10 @@ constexpr uint32_t kRowMask = 0x7FFFFFFFu;
 // block model n = 2^18, F = 128 424 / 458).  The sums are the same either way.
 enum GatherMode { kBuffer = 0, kClasses = 1, kWide = 2, kHalves = 3 };
 
-// Dynamic LDS that keeps a CU to four workgroups where the registers would let five in
-// (kHalves: n = 2^20, F = 64 433 us with five, 425 with four; kWide, n = 2^22, F = 256: 9160
-// and 8968).
+// Dynamic LDS that keeps a CU to four workgroups where the registers would let five or six in
+// (five / four groups, us: kHalves, n = 2^20, F = 64 433 / 425; kClasses with rows of 33 to 64
+// lanes, n = 2^20, F = 128 whole 927 / 861, F = 256 whole 2158 / 1898; kWide, n = 2^22, F = 256
+// 9160 / 8968; classes in 16-lane groups keep five: n = 2^21, F = 128 3309 / 3376).
 constexpr unsigned kFourGroupsLds = 38 * 1024;
 
 // Offset of an entry that reads nothing: past the end of every buffer, also with a lane's
@@ -375,9 +380,9 @@ __device__ __forceinline__ void walk_rounds(const Args &a, int32_t e0, int32_t e
     }
 }
 
-// Dense path: a lane group's sums over its rounds of one row, in V chains (round q of the
-// group adds to chain q % V, by rotating them) that are then added pairwise: as (0 + 2) +
-// (1 + 3) for four, whichever chain is first after the last rotation.
+// Dense path: a lane group's sums over its rounds of one row, in V = 1, 2 or 4 chains (round q
+// of the group adds to chain q % V, by rotating them) that are then added pairwise: as (0 + 2)
+// + (1 + 3) for four, whichever chain is first after the last rotation.
 template <int LPR, int VEC, int MODE, int V>
 __device__ __forceinline__ void dense_rounds(const Args &a, int32_t e0, int32_t e1, int32_t step, int li,
                                              int gbase, int f, bool fin, double (&tot)[VEC]) {
@@ -413,16 +418,33 @@ __device__ __forceinline__ void dense_rounds(const Args &a, int32_t e0, int32_t 
     }
 }
 
-// Entries [e0, e1) of one row by a wavefront: its groups take rounds in turn and a butterfly
-// adds their sums; every lane then holds the sums of its features.  The rounds form four
-// chains (every fourth round), whatever the group's width: four 16-lane groups have one each,
-// wider groups two or four.  So the SpMM's slices of 64 features and the fused kernel, which
-// reads rows whole, add a long row in the same order and give the same bits.
+// Entries [e0, e1) of one row by wavefront `wave` of `waves` that share it: their groups take
+// rounds in turn and a butterfly adds a wavefront's; every lane then holds its sums of its
+// features.  A wavefront's rounds form four chains, whatever the group's width: four 16-lane
+// groups have one each, two 32-lane groups two each, a whole wavefront all four -- one after
+// the other where a round's gathers leave no registers for four sets of sums.  So the SpMM's slices of 64 features and the
+// fused kernel, which reads rows whole, add a long row in the same order and give the same bits.
 template <int LPR, int VEC, int MODE>
-__device__ __forceinline__ void long_row(const Args &a, int32_t e0, int32_t e1, int li, int gw, int gbase,
-                                         int f, bool fin, double (&tot)[VEC]) {
-    constexpr int V = VEC == 4 && LPR > 16 ? LPR / 16 : 1;
-    dense_rounds<LPR, VEC, MODE, V>(a, e0 + gw * kRound, e1, 64 / LPR * kRound, li, gbase, f, fin, tot);
+__device__ __forceinline__ void long_row(const Args &a, int32_t e0, int32_t e1, int wave, int waves, int li,
+                                         int gw, int gbase, int f, bool fin, double (&tot)[VEC]) {
+    if constexpr (VEC == 4 && LPR == 64 && MODE == kBuffer) {
+        double even[VEC], t[VEC];
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {                       // chains 0, 2, 1, 3
+            const int chain = (q >> 1) | ((q & 1) << 1);
+            dense_rounds<LPR, VEC, MODE, 1>(a, e0 + (chain * waves + wave) * kRound, e1, 4 * waves * kRound, li,
+                                            gbase, f, fin, t);
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                if (q % 2 == 0) even[j] = t[j];
+                else tot[j] = q == 1 ? even[j] + t[j] : tot[j] + (even[j] + t[j]);
+            }
+        }
+        return;
+    }
+    constexpr int GPW = 64 / LPR;
+    dense_rounds<LPR, VEC, MODE, VEC == 4 && LPR >= 32 ? LPR / 16 : 1>(
+        a, e0 + (gw * waves + wave) * kRound, e1, GPW * waves * kRound, li, gbase, f, fin, tot);
 #pragma unroll
     for (int m = 32; m >= LPR; m >>= 1)
 #pragma unroll
@@ -440,10 +462,11 @@ __device__ __forceinline__ int32_t task_meta(const int32_t (&m)[N], int j, int g
 }
 
 // The work of logical workgroup lb (feature slice `slice`) for wavefront `wave` of a
-// workgroup of WAVES wavefronts; finished rows go to `emit`.
+// workgroup of WAVES wavefronts; finished rows go to `emit`.  red: (WAVES - 1) x LPR x VEC
+// float64 of LDS, used where wavefronts share a row.
 template <int LPR, int VEC, int WAVES, int MODE, class Emit>
 __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int wave,
-                                           const Emit &emit) {
+                                           const Emit &emit, double *red) {
     constexpr int GPW = 64 / LPR;                 // lane groups per wavefront
     constexpr int RPL = (kTaskRows + LPR - 1) / LPR;
 
@@ -465,11 +488,14 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
         return;
     }
     if (lb < a.nb_parts + a.nb_long) {
-        // ---------------- dense path, long rows: one wavefront per row or per part of a split row
-        const int w = lb * WAVES + wave;
+        // ---------------- dense path, long rows and parts of split rows: a wavefront each, or
+        // the workgroup's wavefronts together
+        constexpr bool kMayShare = MODE == kBuffer || MODE == kHalves;
+        const bool share = kMayShare && a.coop && lb < a.nb_parts + a.nb_coop;
         int32_t i, e0, e1;
         int part = -1, first = 0;
         if (lb < a.nb_parts) {
+            const int w = share ? lb : lb * WAVES + wave;
             if (w >= a.n_parts) return;
             const SplitPart sp = a.parts[a.n_parts - 1 - w];
             i = sp.row;
@@ -478,14 +504,33 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
             e0 = a.pptr[i] + part * a.dense_chunk;
             e1 = min(e0 + a.dense_chunk, a.pptr[i + 1]);
         } else {
-            i = a.n - 1 - (w - a.nb_parts * WAVES);
+            const int q = lb - a.nb_parts;
+            i = a.n - 1 - (share ? q : a.n_coop + (q - a.nb_coop) * WAVES + wave);
             if (i < a.n - a.n_long) return;
             e0 = a.pptr[i];
             e1 = a.pptr[i + 1];
             if (e1 - e0 > a.dense_chunk) return;   // covered by its parts
         }
         double tot[VEC];
-        long_row<LPR, VEC, MODE>(a, e0, e1, li, gw, gbase, f, fin, tot);
+        long_row<LPR, VEC, MODE>(a, e0, e1, share ? wave : 0, share ? WAVES : 1, li, gw, gbase, f, fin, tot);
+        if constexpr (kMayShare) {
+            if (share) {
+                // every wavefront of the workgroup is here with the same row: the first adds
+                // the others' sums in order
+                double *mine = red + li * VEC;
+                if (wave != 0 && gw == 0)
+#pragma unroll
+                    for (int j = 0; j < VEC; ++j) mine[(wave - 1) * LPR * VEC + j] = tot[j];
+                __syncthreads();
+                if (wave == 0)
+#pragma unroll
+                    for (int q = 0; q < WAVES - 1; ++q)
+#pragma unroll
+                        for (int j = 0; j < VEC; ++j) tot[j] += mine[q * LPR * VEC + j];
+                __syncthreads();                  // red is free for the next row
+                if (wave != 0) return;
+            }
+        }
         if (part < 0) {
             if (gw == 0) emit.row(a.perm[i], 0, tot, f, fin);
             return;
@@ -562,9 +607,10 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
 template <int LPR, int VEC, bool BF, int MODE>
 __global__ __launch_bounds__(kThreads) void spmm_dual_kernel(const Args a) {
     const StoreRows<VEC, BF> emit{a.Y, a.ld, a.relu != 0};
+    __shared__ double red[MODE == kBuffer || MODE == kHalves ? (kWaves - 1) * LPR * VEC : 1];
     spmm_block<LPR, VEC, kWaves, MODE>(
         a, static_cast<int>(blockIdx.x) / a.S, static_cast<int>(blockIdx.x) % a.S,
-        static_cast<int>(threadIdx.x) >> 6, emit);
+        static_cast<int>(threadIdx.x) >> 6, emit, red);
 }
 
 // The rows split into parts: row = the sum of its parts' float64 partials, in part order.
@@ -649,6 +695,7 @@ void spmm_xw_kernel(const Args a, const float *__restrict__ W,
     const bool stage_in_tile = xw_stage_in_tile(K);
     float *stage_own = reinterpret_cast<float *>(reinterpret_cast<int32_t *>(xw_lds + (N + kWaves * ROWS) * ld) +
                                                  kWaves * ROWS) + wave * kXwStageWords;
+    __shared__ double red[MODE == kBuffer ? (kWaves - 1) * LPR * 4 : 1];
     for (int idx = static_cast<int>(threadIdx.x); idx < K * N; idx += kThreads) {
         const int c = idx / N, j = idx % N;   // consecutive threads read consecutive columns
         wt[j * ld + c] = to_bf16(W[idx]);
@@ -659,7 +706,7 @@ void spmm_xw_kernel(const Args a, const float *__restrict__ W,
     const StageRows emit{h, outs, ld, a.relu != 0, lane % LPR == 0, static_cast<unsigned short *>(a.Y), a.ld};
     constexpr int KF = LPR / 8;               // A fragments of a row: K <= 4 LPR, 32 k each
     for (int lb = static_cast<int>(blockIdx.x); lb < nblocks; lb += static_cast<int>(gridDim.x)) {
-        spmm_block<LPR, 4, kWaves, MODE>(a, lb, 0, wave, emit);
+        spmm_block<LPR, 4, kWaves, MODE>(a, lb, 0, wave, emit, red);
         __syncwarp();
         // the lane's MFMA coordinates, recomputed here (hidden from the optimiser) rather
         // than held in registers through the aggregation
@@ -762,8 +809,9 @@ __global__ __launch_bounds__(kThreads) void combine_xw_kernel(const Args a, cons
 template <int LPR>
 int64_t schedule_blocks(Args &a) {
     constexpr int GPB = kThreads / LPR;       // sparse tasks per workgroup
-    a.nb_parts = (a.n_parts + kWaves - 1) / kWaves;
-    a.nb_long = (a.n_long + kWaves - 1) / kWaves;
+    a.nb_parts = a.coop ? a.n_parts : (a.n_parts + kWaves - 1) / kWaves;
+    a.nb_coop = a.n_coop;
+    a.nb_long = a.nb_coop + (a.n_long - a.n_coop + kWaves - 1) / kWaves;
     a.nb_dense = a.nb_long + (a.n - a.n_sparse - a.n_long + GPB - 1) / GPB;
     const int64_t nb_sparse = (static_cast<int64_t>(a.n_tasks) + GPB - 1) / GPB;
     return static_cast<int64_t>(a.nb_parts) + a.nb_dense + nb_sparse;
@@ -800,7 +848,7 @@ int launch_xw_window(Args a, const float *W, float *T, int32_t K, int32_t N, hip
 template <int LPR, int VEC, int MODE>
 int launch_dual(Args a, bool bf, hipStream_t s) {
     const int64_t blocks = schedule_blocks<LPR>(a) * a.S;
-    constexpr unsigned lds = MODE == kHalves || MODE == kWide ? kFourGroupsLds : 0;
+    constexpr unsigned lds = MODE == kHalves || MODE == kWide || (MODE == kClasses && LPR >= 32) ? kFourGroupsLds : 0;
     if (blocks == 0) return DUALGCN_OK;
     if (blocks > 0x7FFFFFFF) return DUALGCN_ERR_UNSUPPORTED;
     if (bf)
@@ -815,9 +863,10 @@ int launch_dual(Args a, bool bf, hipStream_t s) {
 template <int LPR, int VEC>
 int launch_window(Args a, int mode, bool bf, hipStream_t s) {
     constexpr int CLS = LPR >= 8 && VEC == 4 ? kClasses : kBuffer;   // classes: rows of whole 128-byte lines
+    constexpr int HLV = (LPR == 16 || LPR == 64) && VEC == 4 ? kHalves : kBuffer;
     int st;
     if (mode == kWide) st = launch_dual<LPR, VEC, kWide>(a, bf, s);
-    else if (mode == kHalves && LPR == 16) st = launch_dual<LPR, VEC, LPR == 16 ? kHalves : kBuffer>(a, bf, s);
+    else if (mode == kHalves && HLV == kHalves) st = launch_dual<LPR, VEC, HLV>(a, bf, s);
     else if (mode == CLS) st = launch_dual<LPR, VEC, CLS>(a, bf, s);
     else st = launch_dual<LPR, VEC, kBuffer>(a, bf, s);
     if (st) return st;
@@ -872,6 +921,21 @@ int long_row_class(int lpr, int mode, int32_t w) {
     return cls;
 }
 
+// Do a workgroup's wavefronts share each long row?  On small graphs the longest row is the whole
+// launch: a wavefront takes a row of 4,000 entries in 63 rounds (64 features), four
+// together in 16.  Rows of at least 2^kLongRowOctave entries and the parts of split rows are
+// shared while there are no more of them than CUs, so that all of them start at once;
+// beyond that the chip is full without (n = 2^19, 1,160 long rows, F = 128: 409 us alone, 430
+// shared).  Measured (us) alone / shared: n = 30,007, 120 long rows, F = 64 57 / 22, F = 96
+// 103 / 39; n = 20,001, 18 rows, F = 64 24 / 16; n = 2^17, F = 64 (154 split rows) 37.6 / 38.4.
+// By the plan and the addressing alone, so the fused kernel and the SpMM add a row alike.
+void share_rows(const Plan &p, int mode, Args &a) {
+    const bool share = (mode == kBuffer || mode == kHalves) && p.n_long[0] + p.n_split_parts <= device_cus();
+    a.coop = share ? 1 : 0;
+    a.n_coop = share ? p.n_long[0] : 0;
+}
+
+
 // A window of 128, 192 or 256 features whose rows are whole 128-byte lines is cut into slices
 // of 64 features, and workgroup b takes slice b % S: workgroups go to the XCDs in turn, so
 // an XCD reads every second (or fourth) 256-byte piece of the rows and its 4 MiB L2 keeps twice
@@ -899,14 +963,17 @@ bool sliced_window(int32_t ld, int32_t w) {
 // gather_mode sets the buffer's size in `a` and picks the addressing for gathers of w features
 // of rows ld apart: 64-bit addresses when X is too large for a buffer load's 32-bit offsets;
 // classes when the plan marked its cold columns, rows are read whole with 16-byte loads, and X
-// is larger than the memory-side cache; half rounds when it is larger than half that cache.
+// is larger than the memory-side cache; half rounds when it is larger than half that cache (on
+// plans that mark no columns only where rows take a wavefront's whole width).
 int gather_mode(const Plan &p, int32_t ld, int32_t w, bool vec, Args &a) {
     const uint64_t bytes = static_cast<uint64_t>(p.n) * static_cast<uint64_t>(ld) * sizeof(float);
     if (bytes > kMaxBufferBytes) return kWide;
     a.x_bytes = static_cast<uint32_t>(bytes);
-    if (!vec || !p.cold_marked) return kBuffer;
+    const bool whole = w > 128 && !sliced_window(ld, w);      // a wavefront per row piece
+    if (!vec || !(p.cold_marked || whole)) return kBuffer;
     const uint64_t operand = static_cast<uint64_t>(p.n) * static_cast<uint64_t>(w) * sizeof(float);
-    return operand > kGatherClassMinBytes ? kClasses : operand > kGatherClassMinBytes / 2 ? kHalves : kBuffer;
+    if (p.cold_marked && operand > kGatherClassMinBytes) return kClasses;
+    return operand > kGatherClassMinBytes / 2 ? kHalves : kBuffer;
 }
 
 }  // namespace
@@ -959,6 +1026,7 @@ int launch_spmm_xw(const Plan &p, const float *X, const float *W, float *T, void
     const int lpr = window_lpr(F_in);
     const int mode = gather_mode(p, F_in, F_in, true, a);
     a.n_long = p.n_long[long_row_class(lpr, mode, F_in)];
+    share_rows(p, mode, a);
     auto launch = [&](auto width) {
         constexpr int LPR = decltype(width)::value;
         if (mode == kWide) return launch_xw_window<LPR, kWide>(a, W, T, F_in, F_out, s);
@@ -995,6 +1063,7 @@ int launch_spmm(const Plan &p, const float *X, void *Y, int32_t F, bool relu, bo
             // cache classes for the widths whose rows fill whole 128-byte lines
             const int mode = gather_mode(p, F, w, w > 16, a);
             a.n_long = p.n_long[long_row_class(lpr, mode, w)];
+            share_rows(p, mode, a);
             if (lpr == 1) st = launch_window<1, 4>(a, mode, bf, s);
             else if (lpr == 2) st = launch_window<2, 4>(a, mode, bf, s);
             else if (lpr == 4) st = launch_window<4, 4>(a, mode, bf, s);
@@ -1007,6 +1076,7 @@ int launch_spmm(const Plan &p, const float *X, void *Y, int32_t F, bool relu, bo
             a.sw = 64;
             a.S = (w + 63) / 64;
             const int mode = gather_mode(p, F, w, false, a);
+            share_rows(p, mode, a);
             st = launch_window<64, 1>(a, mode, bf, s);
         }
     }

@@ -219,3 +219,40 @@ def test_fused_with_identity_weights_is_the_bf16_spmm(dg, device, name):
     H = dg.spmm(plan, Xd, relu=True, out_bf16=True)
     assert torch.equal(T, H.float())
     plan.destroy()
+
+
+def _long_rows(extra):
+    """2,200 rows of 1-3 random columns, and rows of 511, 512, 513, 1,023, 2,049, 4,096 and
+    4,097 entries, plus `extra` rows of 600: at most 256 long rows share workgroups, more of
+    them get a wavefront each."""
+    gen = np.random.default_rng(23)
+    n = 2200
+    rows = [gen.integers(0, n, gen.integers(1, 4)).tolist() for _ in range(n)]
+    for i, m in enumerate([511, 512, 513, 1023, 2049, 4096, 4097] + [600] * extra):
+        rows[7 * i] = gen.integers(0, n, m).tolist()
+    g = small.from_rows(rows)
+    g.val[:] = gen.standard_normal(g.val.size).astype(np.float32)
+    return g
+
+
+@pytest.mark.parametrize("extra", [0, 248, 300])
+@pytest.mark.parametrize("F_in,F_out", [(32, 32), (64, 32), (96, 32), (128, 64), (160, 32), (256, 64)])
+def test_long_rows_shared_by_a_workgroup(dg, device, extra, F_in, F_out):
+    """Rows that a workgroup's wavefronts share, and the same rows one wavefront each (too many
+    to share): within the SpMM's bound, and the fused kernel bit for bit with the two calls at
+    every group width (slices of 64 features against whole rows)."""
+    g = _long_rows(extra)
+    X = dense.features_normal(g.n, F_in, seed=F_in, stream_id=31)
+    W = _weights(F_in, F_out, seed=3)
+    plan = dg.Plan(*to_dev(g, device), seed=1, walks_per_node=4, walk_len=3)
+    Xd, Wd = torch.from_numpy(X).to(device), torch.from_numpy(W).to(device)
+    Y = dg.spmm(plan, Xd).cpu().numpy().astype(np.float64)
+    Yr, B = oracle.spmm(g, X)
+    assert np.all(np.abs(Y - Yr) <= 1e-5 * B)
+    T2 = _two_calls(dg, plan, Xd, Wd, True)
+    T = torch.empty((g.n, F_out), dtype=torch.float32, device=device)
+    st = dg.lib().dualgcn_spmm_update(plan.handle, Xd.data_ptr(), Wd.data_ptr(), T.data_ptr(), None,
+                                      F_in, F_out, dg.RELU, ctypes.c_void_p(0))
+    torch.cuda.synchronize()
+    assert st == dg.OK
+    assert torch.equal(T, T2)
