@@ -670,8 +670,8 @@ int dualgcn_aggregator_values(const dualgcn_csr *csr, int32_t kind, float eps, f
     if ((st = dgc::alloc_bytes(&scratch, 2 * sizeof(int32_t)))) return st;
     int32_t *flags = static_cast<int32_t *>(scratch);
     st = dgc::hip_status(hipMemsetAsync(flags, 0, 2 * sizeof(int32_t), s));
-    if (!st) st = dgc::validate_csr(csr, flags, nullptr, nullptr, nullptr, s);
-    if (!st) st = dgc::launch_aggregator_values(csr, kind, eps, val, s);
+    if (!st) st = dgc::validate_csr(csr, flags, nullptr, nullptr, nullptr, s, false);
+    if (!st) st = dgc::launch_aggregator_values(csr, kind, eps, flags, val, s);
     int32_t bad = 0;
     if (!st) st = dgc::hip_status(hipMemcpyAsync(&bad, flags, sizeof(bad), hipMemcpyDeviceToHost, s));
     if (!st) st = dgc::hip_status(hipStreamSynchronize(s));

@@ -54,6 +54,29 @@ def test_aggregator_values(dg, device, name, kind, eps):
         assert np.array_equal(v, ref)                 # one correctly rounded division
 
 
+def _tiles(n, lengths, seed):
+    """Rows of the given lengths (cycled) with random columns."""
+    gen = np.random.default_rng(seed)
+    return small.from_rows([gen.integers(0, n, lengths[i % len(lengths)]).tolist() for i in range(n)])
+
+
+@pytest.mark.parametrize("n,lengths", [
+    (1, [1]), (1, [2048]), (1, [2049]), (2, [2048, 1]), (3, [0, 4096, 0]), (700, [0, 0, 0, 7, 0]),
+    (5000, [0] * 999 + [3]),        # tiles that meet more rows than entries
+    (4097, [1]), (300, [0, 31, 5000, 1, 2])])
+@pytest.mark.parametrize("kind", ["gcn", "mean", "sum"])
+def test_aggregator_tiles(dg, device, n, lengths, kind):
+    """Rows that start, end and span at the edges of the kernel's tiles of 2,048 entries."""
+    g = _tiles(n, lengths, 5)
+    rp, c = _dev(g, device)
+    v = dg.aggregator_values(rp, c, kind, 0.25).cpu().numpy()
+    ref = oracle.aggregator_values(g, {"gcn": oracle.AGG_GCN, "mean": oracle.AGG_MEAN,
+                                       "sum": oracle.AGG_SUM}[kind], 0.25)
+    finite = np.isfinite(ref)                       # a column whose own row is empty: 1 / 0
+    assert np.array_equal(np.isfinite(v), finite)
+    assert _ulps(v[finite], ref[finite]).max(initial=0) <= 1
+
+
 @pytest.mark.parametrize("kind", ["mean", "sum"])
 def test_spmm_with_other_aggregators_c2(dg, device, kind):
     g = configs.load_graph("c2")
