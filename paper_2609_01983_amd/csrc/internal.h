@@ -128,7 +128,7 @@ struct Plan {
     int32_t n_split_parts = 0;
     SplitPart *parts = nullptr;        // [n_split_parts]
     double *partials = nullptr;        // [n_split_parts][kMaxSlice]
-    int32_t *tile_row = nullptr;       // [nnz / 4096 + 2] rows of the sorted copy's tiles
+    int32_t *tile_row = nullptr;       // [nnz / copy tile + 2] rows of the sorted copy's tiles
     hipEvent_t ready = nullptr;        // recorded after the sorted copy was written
     mutable std::atomic<bool> ready_seen{false};   // `ready` was found complete
     // the last launch that used the plan on each stream (destroy waits for these)

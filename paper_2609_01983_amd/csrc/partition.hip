@@ -11,9 +11,9 @@
 //                   workgroup folds them                              -> host wait 1
 //   host            K* = least integer >= mu_K + beta sigma_K (exact integers)
 //   radix sort      stable LSD sort of (K_v, v) on 8-bit digits      -> perm
-//   split           n_sparse = lower_bound(sorted K, K*)
 //   processing order  (region, row-length octave, node id): one stable radix pass
-//                   over the node ids on a key of (region, octave) below 64
+//                   over the node ids on a key of (region, octave) below 64; its histogram
+//                   also gives n_sparse = the number of K < K*
 //   row pointers    of the rows in processing order, by a scan
 //   schedule        sparse tasks (runs of at most kTaskRows short rows) and the
 //                   parts of dense rows longer than one dense chunk
@@ -32,6 +32,7 @@
 #include <algorithm>
 #include <cstring>
 #include <thread>
+#include <type_traits>
 
 namespace dgc {
 namespace {
@@ -366,10 +367,9 @@ __global__ __launch_bounds__(kThreads) void scan_reduce_kernel(const uint32_t *_
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-// Exclusive scan of the tile sums by one workgroup (in place); writes the grand total.
+// Exclusive scan of the tile sums by one workgroup (in place).
 __global__ __launch_bounds__(kThreads) void scan_top_kernel(uint32_t *__restrict__ sums,
-                                                            int32_t count,
-                                                            uint32_t *__restrict__ grand) {
+                                                            int32_t count) {
     __shared__ uint32_t shw[kThreads / 64];
     uint32_t carry = 0;
     for (int32_t base = 0; base < count; base += kThreads) {
@@ -380,25 +380,48 @@ __global__ __launch_bounds__(kThreads) void scan_top_kernel(uint32_t *__restrict
         if (i < count) sums[i] = carry + ex;
         carry += total;
     }
-    if (threadIdx.x == 0 && grand) *grand = carry;
 }
 
-// Exclusive scan inside each tile plus the tile's offset; out may alias in.  A full tile is
+// Sum over a 256-thread workgroup; every thread gets it.
+template <typename T>
+__device__ __forceinline__ T block_sum(T x, T *sh_waves) {
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+    if ((threadIdx.x & 63) == 0) sh_waves[threadIdx.x >> 6] = x;
+    __syncthreads();
+    T sum = 0;
+    for (int i = 0; i < kThreads / 64; ++i) sum += sh_waves[i];
+    __syncthreads();
+    return sum;
+}
+
+// Exclusive scan inside each tile plus the tile's offset; out may alias in.  With DIRECT the
+// sums are the tiles' own and every workgroup adds those before its tile (up to kDirectTiles
+// words out of the L2) instead of a launch of one workgroup that scans them.  A full tile is
 // taken as kTile / 4 quads in index order, quad c held by thread c % kThreads in round
 // c / kThreads: round by round, a block scan of the quad sums gives each quad its offset,
 // so loads and stores stay coalesced 16-byte accesses (arrays 16-byte aligned).  Other
 // tiles go element by element, each thread scanning kItems consecutive elements.
+constexpr int64_t kDirectTiles = 4096;
+template <bool DIRECT>
 __global__ __launch_bounds__(kThreads) void scan_apply_kernel(const uint32_t *in, int64_t count,
                                                               const uint32_t *__restrict__ sums,
                                                               uint32_t *out) {
     __shared__ uint32_t shw[kThreads / 64];
     const int64_t tile = static_cast<int64_t>(blockIdx.x) * kTile;
+    uint32_t start;
+    if constexpr (DIRECT) {
+        uint32_t s = 0;
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kThreads) s += sums[i];
+        start = block_sum(s, shw);
+    } else {
+        start = sums[blockIdx.x];
+    }
     if (tile + kTile <= count && (reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) % 16 == 0) {
         const uint4 *q = reinterpret_cast<const uint4 *>(in + tile);
         uint4 v[kItems / 4];
 #pragma unroll
         for (int i = 0; i < kItems / 4; ++i) v[i] = q[threadIdx.x + i * kThreads];
-        uint32_t carry = sums[blockIdx.x];
+        uint32_t carry = start;
 #pragma unroll
         for (int i = 0; i < kItems / 4; ++i) {
             const uint32_t qs = v[i].x + v[i].y + v[i].z + v[i].w;
@@ -418,7 +441,7 @@ __global__ __launch_bounds__(kThreads) void scan_apply_kernel(const uint32_t *in
         s += v[i];
     }
     uint32_t total;
-    uint32_t run = block_exclusive_scan(s, &total, shw) + sums[blockIdx.x];
+    uint32_t run = block_exclusive_scan(s, &total, shw) + start;
     for (int i = 0; i < kItems; ++i) {
         if (base + i < count) out[base + i] = run;
         run += v[i];
@@ -450,7 +473,7 @@ __global__ __launch_bounds__(kThreads) void radix_hist_kernel(const uint64_t *__
     hist[static_cast<int64_t>(threadIdx.x) * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
-// Stable scatter of one 8-bit digit.  Wave w owns items [base + 64 ITEMS w, base + 64 ITEMS
+// Stable scatter of one 8-bit digit (keys_out null: the values only).  Wave w owns items [base + 64 ITEMS w, base + 64 ITEMS
 // (w+1)), taken in rounds of 64 consecutive items; lanes with equal digits find each other
 // with eight ballots, so an item's rank is (earlier items of its digit in this wave) +
 // (earlier lanes of its digit in this round).  Tile order = index order, hence stable.
@@ -504,7 +527,7 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
             const uint32_t dg = static_cast<uint32_t>((key >> shift) & (kRadix - 1));
             const uint32_t dest = goff[dg] + cnt[wave][dg] + rank[j];
             if (dest < static_cast<uint32_t>(n)) {   // always true for a consistent histogram
-                keys_out[dest] = key;
+                if (keys_out) keys_out[dest] = key;
                 vals_out[dest] = vals_in ? vals_in[idx] : static_cast<int32_t>(idx);
             }
         }
@@ -526,83 +549,63 @@ struct SplitSummary {
     int32_t long_rows[kLongRowClasses];   // dense rows of >= 2^(kLongRowOctave - c) entries
 };
 
-// First index i of the sorted array a[0, n) with a[i] >= x (n if none), found by one
-// wavefront: each round probes 64 evenly spaced positions strictly inside the candidate
-// range [lo, hi] (a[i] < x below lo, a[i] >= x from hi on) and keeps the gap between the
-// last probe below x and the first one at or above it, until at most 64 candidates are left.
-__device__ int32_t wave_lower_bound(const uint64_t *__restrict__ a, int32_t n, uint64_t x) {
-    const int lane = static_cast<int>(threadIdx.x) & 63;
-    int32_t lo = 0, hi = n;
-    while (hi - lo > 64) {
-        const int64_t span = hi - lo;
-        const int32_t p = lo + static_cast<int32_t>(span * (lane + 1) / 65);
-        const uint64_t m = __ballot(a[p] >= x);
-        if (m == 0) {
-            lo = lo + static_cast<int32_t>(span * 64 / 65) + 1;
-        } else {
-            const int f = __ffsll(static_cast<unsigned long long>(m)) - 1;
-            hi = lo + static_cast<int32_t>(span * (f + 1) / 65);
-            if (f > 0) lo = lo + static_cast<int32_t>(span * f / 65) + 1;
-        }
-    }
-    const int32_t p = lo + lane;
-    const uint64_t m = __ballot(p >= hi || a[p] >= x);
-    return m ? lo + __ffsll(static_cast<unsigned long long>(m)) - 1 : hi;
-}
-
-// n_sparse = first position whose key is >= K* (one wavefront; keys are sorted).
-__global__ void lower_bound_kernel(const uint64_t *__restrict__ sorted, int32_t n, uint64_t kstar,
-                                   int32_t force_sparse_count, SplitSummary *__restrict__ out) {
-    const int32_t lo = wave_lower_bound(sorted, n, kstar);
-    if (threadIdx.x != 0) return;
-    out->n_sparse = force_sparse_count >= 0 ? force_sparse_count : lo;
-    out->split_rows = 0;
-    out->parts = 0;
-    out->tasks = 0;
-    for (int c = 0; c < kLongRowClasses; ++c) out->long_rows[c] = 0;
-}
-
-// long_rows[c] = rows of the dense region with at least 2^(kLongRowOctave - c) entries: the
-// rows whose processing-order key is at least that class's, i.e. n minus the number of
-// smaller keys, which the scanned histogram of the order pass holds (digit-major: entry
-// d * nblocks is the count of keys below d).
-__global__ void long_rows_kernel(const uint32_t *__restrict__ scanned_hist, int32_t nblocks,
-                                 int32_t n, SplitSummary *__restrict__ out) {
-    const int c = static_cast<int>(threadIdx.x);
-    if (c >= kLongRowClasses) return;
-    const uint32_t first_long = 32u + kLongRowOctave - c;
-    out->long_rows[c] = n - static_cast<int32_t>(scanned_hist[static_cast<int64_t>(first_long) * nblocks]);
-}
-
 // Processing order of the SpMM (the row order of the sorted copy): region first (sparse
 // rows, then dense rows, Eq. (1)), then the octave of the row length, then node id.  Rows
 // that share an octave cost about the same (the balance the paper sorts for); keeping node
 // ids in order inside an octave keeps whatever locality the numbering has (e.g. the
 // contiguous communities of a block-structured graph).  forced = 0 / 1 puts every row in
 // one region, -1 applies K >= K*.
-__global__ __launch_bounds__(kThreads) void order_key_kernel(const uint64_t *__restrict__ K,
-                                                             uint64_t kstar, int32_t forced,
-                                                             const int32_t *__restrict__ rowptr,
-                                                             int32_t n, uint64_t *__restrict__ key) {
-    const int64_t v = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    const uint32_t deg = static_cast<uint32_t>(rowptr[v + 1] - rowptr[v]);
-    const uint64_t octave = deg ? 31u - static_cast<uint32_t>(__clz(deg)) : 0u;
-    const uint64_t dense = forced >= 0 ? static_cast<uint64_t>(forced) : (K[v] >= kstar ? 1u : 0u);
-    key[v] = dense * 32u + octave;
+// The digit histogram of these keys (one 8-bit pass) is taken in the same launch.
+template <int ITEMS>
+__global__ __launch_bounds__(kThreads) void order_hist_kernel(const uint64_t *__restrict__ K,
+                                                              uint64_t kstar, int32_t forced,
+                                                              const int32_t *__restrict__ rowptr, int32_t n,
+                                                              uint64_t *__restrict__ key,
+                                                              uint32_t *__restrict__ hist, int32_t nblocks) {
+    __shared__ uint32_t h[kRadix];
+    h[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * kThreads * ITEMS;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const int64_t v = base + static_cast<int64_t>(i) * kThreads + threadIdx.x;
+        if (v < n) {
+            const uint32_t deg = static_cast<uint32_t>(rowptr[v + 1] - rowptr[v]);
+            const uint32_t octave = deg ? 31u - static_cast<uint32_t>(__clz(deg)) : 0u;
+            const uint32_t dense = forced >= 0 ? static_cast<uint32_t>(forced) : (K[v] >= kstar ? 1u : 0u);
+            key[v] = dense * 32u + octave;
+            atomicAdd(&h[dense * 32u + octave], 1u);
+        }
+    }
+    __syncthreads();
+    hist[static_cast<int64_t>(threadIdx.x) * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
 // pptr[i] = length of row order[i] for i < n and pptr[n] = 0; an exclusive scan then turns
-// pptr into the row pointers of the sorted copy.
+// pptr into the row pointers of the sorted copy.  The first workgroup also starts the summary
+// from the scanned histogram of the order pass (digit-major: entry d * nblocks is the count
+// of keys below d): n_sparse is the number of keys of the sparse region (below 32), i.e. of
+// K < K*, and long_rows[c] the number of rows whose key is at least the class's in the dense
+// region.
 __global__ __launch_bounds__(kThreads) void sorted_degree_kernel(const int32_t *__restrict__ order,
                                                                  const int32_t *__restrict__ rowptr,
-                                                                 int32_t n, uint32_t *__restrict__ pptr) {
+                                                                 int32_t n, uint32_t *__restrict__ pptr,
+                                                                 const uint32_t *__restrict__ scanned_hist,
+                                                                 int32_t nblocks, SplitSummary *__restrict__ out) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) {
         const int32_t r = order[i];
         pptr[i] = static_cast<uint32_t>(rowptr[r + 1] - rowptr[r]);
     } else if (i == n) {
         pptr[n] = 0;
+    }
+    if (i < kLongRowClasses) {
+        const uint32_t first_long = 32u + kLongRowOctave - static_cast<uint32_t>(i);
+        out->long_rows[i] = n - static_cast<int32_t>(scanned_hist[static_cast<int64_t>(first_long) * nblocks]);
+    }
+    if (i == 0) {
+        out->n_sparse = static_cast<int32_t>(scanned_hist[static_cast<int64_t>(32) * nblocks]);
+        out->split_rows = 0;
     }
 }
 
@@ -618,43 +621,37 @@ __device__ __forceinline__ int32_t row_of(const P &ptr, int32_t lo, int32_t hi, 
     return lo;
 }
 
-constexpr int kCopyTile = 4096;     // entries of the sorted copy one workgroup fills
+// Entries of the sorted copy one workgroup fills: 4,096, and 1,024 below kCopySmallNnz entries,
+// where tiles of 4,096 leave most CUs idle (1.3M entries: 19.1 -> 9.6 us).
+constexpr int kCopyTile = 4096;
+constexpr int kCopyTileSmall = 1024;
+constexpr int64_t kCopySmallNnz = int64_t{1} << 23;
 
-// tile_row[t] = the sorted row that holds entry t kCopyTile (for every tile start below nnz):
-// each non-empty row writes the tiles that start inside it.
-__global__ __launch_bounds__(kThreads) void tile_row_kernel(const int32_t *__restrict__ pptr,
-                                                            int32_t n, int32_t *__restrict__ tile_row) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t b = pptr[i], e = pptr[i + 1];
-    for (int64_t t = (b + kCopyTile - 1) / kCopyTile; t * kCopyTile < e; ++t)
-        tile_row[t] = static_cast<int32_t>(i);
-}
-
-// Fills entries [b kCopyTile, (b + 1) kCopyTile) of the sorted copy: entry e of sorted
+// Fills entries [b TILE, (b + 1) TILE) of the sorted copy: entry e of sorted
 // row i is entry e - pptr[i] of row order[i], i.e. entry e + delta[i] of the matrix with
 // delta[i] = rowptr[order[i]] - pptr[i].  The tile's rows come from tile_row; each counts
 // itself at the tile position where it starts (its first entry, or the tile's start), and
 // an inclusive scan of those counts gives every entry the index of its row (rows of no
 // entries start where the next row does and count before it).  Thread t then copies entries
 // e0 + t + 256 k, so reads inside a row and all writes are coalesced.
+template <int TILE>
 __global__ __launch_bounds__(kThreads) void sorted_copy_kernel(
     const int32_t *__restrict__ order, const int32_t *__restrict__ rowptr,
     const int32_t *__restrict__ col, const float *__restrict__ val,
     const int32_t *__restrict__ pptr, const int32_t *__restrict__ tile_row, int32_t n,
     int64_t nnz, int32_t *__restrict__ pcol, float *__restrict__ pval) {
-    constexpr int kPer = kCopyTile / kThreads;          // counters one thread scans
-    __shared__ int32_t sh_delta[kCopyTile + 1];
-    __shared__ __align__(16) uint32_t sh_cnt[kCopyTile];
+    constexpr int kPer = TILE / kThreads;          // counters one thread scans
+    __shared__ int32_t sh_delta[TILE + 1];
+    __shared__ __align__(16) uint32_t sh_cnt[TILE];
     __shared__ uint32_t sh_waves[kThreads / 64];
     const int t = static_cast<int>(threadIdx.x);
-    const int64_t e0 = static_cast<int64_t>(blockIdx.x) * kCopyTile;
-    const int64_t e1 = e0 + kCopyTile < nnz ? e0 + kCopyTile : nnz;
+    const int64_t e0 = static_cast<int64_t>(blockIdx.x) * TILE;
+    const int64_t e1 = e0 + TILE < nnz ? e0 + TILE : nnz;
     const int32_t r_lo = tile_row[blockIdx.x];
     const int32_t r_hi = e1 < nnz ? tile_row[blockIdx.x + 1] : n - 1;   // holds e1 or the end
     const int32_t rows = r_hi - r_lo + 1;
-    if (rows <= kCopyTile + 1) {
-        for (int k = t; k < kCopyTile; k += kThreads) sh_cnt[k] = 0;
+    if (rows <= TILE + 1) {
+        for (int k = t; k < TILE; k += kThreads) sh_cnt[k] = 0;
         __syncthreads();
         for (int32_t k = t; k < rows; k += kThreads) {
             const int32_t b = pptr[r_lo + k];
@@ -731,64 +728,123 @@ __device__ __forceinline__ bool starts_task(const int32_t *__restrict__ pptr, in
     return (i - lo) % kTaskRows == 0;
 }
 
-// flags[i] = offsets[i] = 1 if row i starts a task (offsets is scanned afterwards).
-__global__ __launch_bounds__(kThreads) void task_flag_kernel(const int32_t *__restrict__ pptr,
-                                                             int32_t n,
-                                                             const SplitSummary *__restrict__ sum,
-                                                             uint32_t *__restrict__ flags,
-                                                             uint32_t *__restrict__ offsets) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t f = (i < sum->n_sparse && starts_task(pptr, static_cast<int32_t>(i))) ? 1u : 0u;
-    flags[i] = f;
-    offsets[i] = f;
+// The schedule in two launches over tiles of kThreads * ITEMS rows of the sorted order.
+//
+// Count: cnt[i] = 2 (parts of row i) + (row i starts a task), where a dense row longer than one
+// chunk has ceil(length / chunk) parts; tile_sums[b] = the tile's tasks in the low and its
+// parts in the high 32 bits (both totals stay below 2^31).
+template <int ITEMS>
+__global__ __launch_bounds__(kThreads) void schedule_count_kernel(const int32_t *__restrict__ pptr, int32_t n,
+                                                                  int32_t chunk, SplitSummary *__restrict__ sum,
+                                                                  uint32_t *__restrict__ cnt,
+                                                                  uint64_t *__restrict__ tile_sums) {
+    __shared__ uint64_t shw[kThreads / 64];
+    const int32_t n_sparse = sum->n_sparse;
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * kThreads * ITEMS;
+    uint64_t s = 0;
+    for (int k = 0; k < ITEMS; ++k) {
+        const int64_t i = base + static_cast<int64_t>(k) * kThreads + threadIdx.x;
+        if (i >= n) break;
+        uint32_t c = 0;
+        if (i < n_sparse) {
+            c = starts_task(pptr, static_cast<int32_t>(i)) ? 1u : 0u;
+        } else {
+            const int32_t deg = pptr[i + 1] - pptr[i];
+            if (deg > chunk) {
+                c = 2u * static_cast<uint32_t>((deg + chunk - 1) / chunk);
+                atomicAdd(&sum->split_rows, 1);
+            }
+        }
+        cnt[i] = c;
+        s += (c & 1u) | (static_cast<uint64_t>(c >> 1) << 32);
+    }
+    s = block_sum(s, shw);
+    if (threadIdx.x == 0) tile_sums[blockIdx.x] = s;
 }
 
-// tasks[offsets[i]] = i for every task start i; tasks[n_tasks] = n_sparse.
-__global__ __launch_bounds__(kThreads) void task_fill_kernel(int32_t n,
-                                                             const SplitSummary *__restrict__ sum,
-                                                             const uint32_t *__restrict__ flags,
-                                                             const uint32_t *__restrict__ offsets,
-                                                             int32_t *__restrict__ tasks) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i == 0) tasks[sum->tasks] = sum->n_sparse;
-    if (i < n && flags[i]) tasks[offsets[i]] = static_cast<int32_t>(i);
+// More than kDirectTiles tiles: their sums scanned in place by one workgroup, 256 at a time.
+__global__ __launch_bounds__(kThreads) void schedule_top_kernel(uint64_t *__restrict__ tile_sums, int32_t count) {
+    __shared__ uint64_t sh[kThreads];
+    const int t = static_cast<int>(threadIdx.x);
+    uint64_t carry = 0;
+    for (int32_t base = 0; base < count; base += kThreads) {
+        const uint64_t x = base + t < count ? tile_sums[base + t] : 0;
+        sh[t] = x;
+        __syncthreads();
+        for (int d = 1; d < kThreads; d <<= 1) {
+            const uint64_t y = t >= d ? sh[t - d] : 0;
+            __syncthreads();
+            sh[t] += y;
+            __syncthreads();
+        }
+        if (base + t < count) tile_sums[base + t] = carry + sh[t] - x;
+        carry += sh[kThreads - 1];
+        __syncthreads();
+    }
 }
 
-// Dense rows of the sorted order longer than one chunk: counts[i] = offsets[i] = number of
-// parts (offsets is scanned afterwards).
-__global__ __launch_bounds__(kThreads) void split_count_kernel(const int32_t *__restrict__ pptr,
-                                                               int32_t n, int32_t chunk,
-                                                               SplitSummary *__restrict__ sum,
-                                                               uint32_t *__restrict__ counts,
-                                                               uint32_t *__restrict__ offsets) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    uint32_t c = 0;
-    if (i >= sum->n_sparse) {
-        const int32_t deg = pptr[i + 1] - pptr[i];
-        if (deg > chunk) {
-            c = static_cast<uint32_t>((deg + chunk - 1) / chunk);
-            atomicAdd(&sum->split_rows, 1);
+// Fill: every workgroup adds the sums of the tiles before its own (or takes the scanned one,
+// past kDirectTiles tiles), scans its rows' counts and
+// writes their tasks (tasks[n_tasks] = n_sparse) and parts.  Non-empty rows also write the
+// tiles of the sorted copy that start inside them: tile_row[t] = the sorted row that holds
+// entry t * copy_tile.  Thread t takes ITEMS consecutive rows.  (Six counting, scanning and
+// filling launches for tasks and parts each, and one for tile_row, before: 1.3M entries, n =
+// 2^17, 13 launches of 2-4 us.)
+template <int ITEMS>
+__global__ __launch_bounds__(kThreads) void schedule_fill_kernel(const int32_t *__restrict__ pptr, int32_t n,
+                                                                 SplitSummary *__restrict__ sum,
+                                                                 const uint32_t *__restrict__ cnt,
+                                                                 const uint64_t *__restrict__ tile_sums,
+                                                                 int32_t *__restrict__ tasks,
+                                                                 SplitPart *__restrict__ parts, uint32_t max_parts,
+                                                                 int32_t copy_tile, int32_t *__restrict__ tile_row,
+                                                                 int32_t scanned) {
+    __shared__ uint64_t shw[kThreads / 64];
+    uint64_t before = 0;
+    if (scanned) {
+        before = tile_sums[blockIdx.x];
+    } else {
+        for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kThreads) before += tile_sums[b];
+        before = block_sum(before, shw);
+    }
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * kThreads * ITEMS + static_cast<int64_t>(threadIdx.x) * ITEMS;
+    uint32_t c[ITEMS];
+    uint64_t s = 0;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        c[k] = base + k < n ? cnt[base + k] : 0u;
+        s += (c[k] & 1u) | (static_cast<uint64_t>(c[k] >> 1) << 32);
+    }
+    // exclusive scan of s over the workgroup
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint64_t inc = s;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint64_t y = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += y;
+    }
+    if (lane == 63) shw[wave] = inc;
+    __syncthreads();
+    uint64_t at = before + inc - s;
+    for (int w = 0; w < wave; ++w) at += shw[w];
+    for (int k = 0; k < ITEMS; ++k) {
+        const int64_t i = base + k;
+        if (i >= n) break;
+        const uint32_t task = static_cast<uint32_t>(at), part = static_cast<uint32_t>(at >> 32);
+        if (c[k] & 1u) tasks[task] = static_cast<int32_t>(i);
+        const uint32_t m = c[k] >> 1;
+        for (uint32_t j = 0; j < m && part + j < max_parts; ++j)
+            parts[part + j] = SplitPart{static_cast<int32_t>(i), static_cast<int32_t>(j),
+                                        static_cast<int32_t>(m), static_cast<int32_t>(part)};
+        at += (c[k] & 1u) | (static_cast<uint64_t>(m) << 32);
+        const int64_t b = pptr[i], e = pptr[i + 1];
+        for (int64_t t = (b + copy_tile - 1) / copy_tile; t * copy_tile < e; ++t)
+            tile_row[t] = static_cast<int32_t>(i);
+        if (i == n - 1) {
+            sum->tasks = static_cast<uint32_t>(at);
+            sum->parts = static_cast<uint32_t>(at >> 32);
+            tasks[static_cast<uint32_t>(at)] = sum->n_sparse;
         }
     }
-    counts[i] = c;
-    offsets[i] = c;        // scanned afterwards
-}
-
-__global__ __launch_bounds__(kThreads) void split_fill_kernel(const uint32_t *__restrict__ counts,
-                                                              const uint32_t *__restrict__ offsets,
-                                                              int32_t n,
-                                                              SplitPart *__restrict__ parts,
-                                                              uint32_t n_parts) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t c = counts[i];
-    if (c == 0) return;
-    const uint32_t off = offsets[i];
-    for (uint32_t j = 0; j < c && off + j < n_parts; ++j)
-        parts[off + j] = SplitPart{static_cast<int32_t>(i), static_cast<int32_t>(j),
-                                   static_cast<int32_t>(c), static_cast<int32_t>(off)};
 }
 
 // ------------------------------------------------------------------ host helpers
@@ -869,21 +925,19 @@ int read_back(void *dst, const void *src, size_t bytes, hipStream_t s) {
     return st;
 }
 
-// Exclusive scan of `count` u32 values in place; `sums` holds one word per tile.
-// Writes the grand total to *grand (device) when grand is not null.
-int exclusive_scan(uint32_t *data, int64_t count, uint32_t *sums, uint32_t *grand,
-                   hipStream_t s) {
+// Exclusive scan of `count` u32 values in place; `sums` holds one word per tile: one launch for
+// a single tile, two up to kDirectTiles tiles (16.8M values), else three.
+int exclusive_scan(uint32_t *data, int64_t count, uint32_t *sums, hipStream_t s) {
     const int64_t tiles = (count + kTile - 1) / kTile;
     if (tiles > 0x7FFFFFFF) return DUALGCN_ERR_UNSUPPORTED;
-    if (tiles > 0) {
-        hipLaunchKernelGGL(scan_reduce_kernel, dim3(static_cast<unsigned>(tiles)), dim3(kThreads),
-                           0, s, data, count, sums);
-    }
-    hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(kThreads), 0, s, sums,
-                       static_cast<int32_t>(tiles), grand);
-    if (tiles > 0) {
-        hipLaunchKernelGGL(scan_apply_kernel, dim3(static_cast<unsigned>(tiles)), dim3(kThreads),
-                           0, s, data, count, sums, data);
+    if (tiles == 0) return DUALGCN_OK;
+    const dim3 grid(static_cast<unsigned>(tiles)), block(kThreads);
+    if (tiles > 1) hipLaunchKernelGGL(scan_reduce_kernel, grid, block, 0, s, data, count, sums);
+    if (tiles <= kDirectTiles) {
+        hipLaunchKernelGGL(scan_apply_kernel<true>, grid, block, 0, s, data, count, sums, data);
+    } else {
+        hipLaunchKernelGGL(scan_top_kernel, dim3(1), block, 0, s, sums, static_cast<int32_t>(tiles));
+        hipLaunchKernelGGL(scan_apply_kernel<false>, grid, block, 0, s, data, count, sums, data);
     }
     return hip_status(hipGetLastError());
 }
@@ -1128,6 +1182,7 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
     const int32_t nblocks = static_cast<int32_t>((static_cast<int64_t>(n) + sort_tile - 1) / sort_tile);
     const int64_t scan_tiles = std::max((static_cast<int64_t>(kRadix) * nblocks + kTile - 1) / kTile,
                                         (static_cast<int64_t>(n) + 1 + kTile - 1) / kTile) + 1;
+    const int32_t copy_tile = nnz < kCopySmallNnz ? kCopyTileSmall : kCopyTile;
     Layout lp, ls;
     const size_t o_S = lp.take(sizeof(uint32_t) * un), o_K = lp.take(sizeof(uint64_t) * un),
                  o_perm = lp.take(sizeof(int32_t) * un), o_order = lp.take(sizeof(int32_t) * un),
@@ -1136,7 +1191,7 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
                  o_tasks = lp.take(sizeof(int32_t) * (un + 1)),
                  o_parts = lp.take(sizeof(SplitPart) * max_parts),
                  o_partials = lp.take(sizeof(double) * max_parts * kMaxSlice),
-                 o_tiles = lp.take(sizeof(int32_t) * (unnz / kCopyTile + 2));
+                 o_tiles = lp.take(sizeof(int32_t) * (unnz / static_cast<size_t>(copy_tile) + 2));
     // the validation flags and the heat histogram are cleared by one fill; the hot heat
     // value follows them
     constexpr size_t kFlagBytes = 2 * sizeof(int32_t), kHistBytes = sizeof(uint32_t) * kHeatLevels;
@@ -1145,7 +1200,8 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
                  o_kb1 = ls.take(sizeof(uint64_t) * un), o_vb0 = ls.take(sizeof(int32_t) * un),
                  o_scan = ls.take(sizeof(uint32_t) * static_cast<size_t>(scan_tiles)),
                  o_hist = ls.take(sizeof(uint32_t) * kRadix * static_cast<size_t>(nblocks)),
-                 o_ssum = ls.take(sizeof(SplitSummary)), o_counts = ls.take(sizeof(uint32_t) * 2 * ((un + 3) / 4 * 4)),
+                 o_ssum = ls.take(sizeof(SplitSummary)), o_counts = ls.take(sizeof(uint32_t) * un),
+                 o_tsums = ls.take(sizeof(uint64_t) * static_cast<size_t>(nblocks)),
                  o_info = ls.take(sizeof(int2) * un),
                  o_succ = ls.take(use_succ ? sizeof(int2) * unnz : 0),
                  o_marked = ls.take(mark ? sizeof(int32_t) * unnz : 0),
@@ -1199,7 +1255,7 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
     };
     SplitSummary *dsum = reinterpret_cast<SplitSummary *>(sm + o_ssum);
     uint32_t *cnt = reinterpret_cast<uint32_t *>(sm + o_counts);
-    uint32_t *off = cnt + (static_cast<int64_t>(n) + 3) / 4 * 4;    // 16-byte aligned
+    uint64_t *tile_sums = reinterpret_cast<uint64_t *>(sm + o_tsums);
     int2 *nodeinfo = reinterpret_cast<int2 *>(sm + o_info);
     int32_t *blockmax = reinterpret_cast<int32_t *>(sm + o_bmax);
 
@@ -1282,7 +1338,7 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
         if ((st = hip_status(hipMemsetAsync(p->perm, 0, sizeof(int32_t) * un, s)))) return st;
         radix_hist(p->K, 0);
         if ((st = hip_status(hipGetLastError()))) return st;
-        if ((st = exclusive_scan(hist, static_cast<int64_t>(kRadix) * nblocks, scan_sums, nullptr, s)))
+        if ((st = exclusive_scan(hist, static_cast<int64_t>(kRadix) * nblocks, scan_sums, s)))
             return st;
         if ((st = wait_event(sums_read.e))) return st;
         std::memcpy(&sum, pin, sizeof(sum));
@@ -1300,14 +1356,9 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
     // stable radix sort of (K, v) on the bits the keys use (the first digit's histogram and
     // scan are already queued)
     const int passes = (bit_length(p->kmax) + kRadixBits - 1) / kRadixBits;
-    uint64_t *sorted = nullptr;
     if (passes == 0) {
         hipLaunchKernelGGL(iota_kernel, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0, s,
                            p->perm, n);
-        if ((st = hip_status(hipMemcpyAsync(kb0, p->K, sizeof(uint64_t) * un,
-                                            hipMemcpyDeviceToDevice, s))))
-            return st;
-        sorted = kb0;
     } else {
         // ping-pong so that the last pass lands its values in p->perm
         int32_t *vbuf[2];
@@ -1323,13 +1374,12 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
         const int32_t *vin = nullptr;   // identity on the first pass
         for (int pass = 0; pass < passes; ++pass) {
             const int shift = pass * kRadixBits;
-            uint64_t *kout = kbuf[pass % 2];
+            uint64_t *kout = pass + 1 < passes ? kbuf[pass % 2] : nullptr;   // only the order is kept
             int32_t *vout = vbuf[pass % 2];
             if (pass > 0) {
                 radix_hist(kin, shift);
                 if ((st = hip_status(hipGetLastError()))) return st;
-                if ((st = exclusive_scan(hist, static_cast<int64_t>(kRadix) * nblocks, scan_sums,
-                                         nullptr, s)))
+                if ((st = exclusive_scan(hist, static_cast<int64_t>(kRadix) * nblocks, scan_sums, s)))
                     return st;
             }
             radix_scatter(kin, vin, shift, kout, vout);
@@ -1337,47 +1387,43 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
             kin = kout;
             vin = vout;
         }
-        sorted = const_cast<uint64_t *>(kin);
     }
 
     // region split, the sorted copy of the matrix, sparse tasks and dense-row parts
-    int32_t forced = -1;
-    if (th.force_mode == DUALGCN_FORCE_SPARSE) forced = n;
-    if (th.force_mode == DUALGCN_FORCE_DENSE) forced = 0;
-    hipLaunchKernelGGL(lower_bound_kernel, dim3(1), dim3(64), 0, s, sorted, n, p->kstar, forced, dsum);
     const unsigned grid_n1 = static_cast<unsigned>((static_cast<int64_t>(n) + 1 + kThreads - 1) / kThreads);
-    const unsigned grid_n = static_cast<unsigned>((static_cast<int64_t>(n) + kThreads - 1) / kThreads);
-    // processing order: one stable 8-bit pass over the node ids (keys < 64); the buffer of
-    // the sorted keys is free again once lower_bound has run (same stream)
+    // processing order: one stable 8-bit pass over the node ids (keys < 64); the buffers of
+    // the sorted keys are free again
     {
         const int32_t region = th.force_mode == DUALGCN_FORCE_SPARSE ? 0
                                : th.force_mode == DUALGCN_FORCE_DENSE ? 1 : -1;
-        uint64_t *okey = sorted == kb0 ? kb1 : kb0;
-        uint64_t *okey_out = sorted == kb0 ? kb0 : kb1;
-        hipLaunchKernelGGL(order_key_kernel, dim3(grid_n), dim3(kThreads), 0, s, p->K, p->kstar,
-                           region, csr->rowptr, n, okey);
-        radix_hist(okey, 0);
-        if ((st = exclusive_scan(hist, static_cast<int64_t>(kRadix) * nblocks, scan_sums, nullptr, s)))
-            return st;
-        radix_scatter(okey, nullptr, 0, okey_out, p->order);
-        hipLaunchKernelGGL(long_rows_kernel, dim3(1), dim3(64), 0, s, hist, nblocks, n, dsum);
+        if (sort_items == kItems)
+            hipLaunchKernelGGL(order_hist_kernel<kItems>, dim3(nblocks), dim3(kThreads), 0, s, p->K, p->kstar,
+                               region, csr->rowptr, n, kb0, hist, nblocks);
+        else
+            hipLaunchKernelGGL(order_hist_kernel<kSortItemsSmall>, dim3(nblocks), dim3(kThreads), 0, s, p->K,
+                               p->kstar, region, csr->rowptr, n, kb0, hist, nblocks);
+        if ((st = exclusive_scan(hist, static_cast<int64_t>(kRadix) * nblocks, scan_sums, s))) return st;
+        radix_scatter(kb0, nullptr, 0, nullptr, p->order);
         if ((st = hip_status(hipGetLastError()))) return st;
     }
     uint32_t *pptr_u = reinterpret_cast<uint32_t *>(p->pptr);
     phase.next("partition: sorted copy + schedule");
     hipLaunchKernelGGL(sorted_degree_kernel, dim3(grid_n1), dim3(kThreads), 0, s, p->order, csr->rowptr,
-                       n, pptr_u);
-    if ((st = exclusive_scan(pptr_u, static_cast<int64_t>(n) + 1, scan_sums, nullptr, s))) return st;
-    hipLaunchKernelGGL(task_flag_kernel, dim3(grid_n), dim3(kThreads), 0, s, p->pptr, n, dsum, cnt,
-                       off);
-    if ((st = exclusive_scan(off, n, scan_sums, &dsum->tasks, s))) return st;
-    hipLaunchKernelGGL(task_fill_kernel, dim3(grid_n), dim3(kThreads), 0, s, n, dsum, cnt, off,
-                       p->tasks);
-    hipLaunchKernelGGL(split_count_kernel, dim3(grid_n), dim3(kThreads), 0, s, p->pptr, n,
-                       p->dense_chunk, dsum, cnt, off);
-    if ((st = exclusive_scan(off, n, scan_sums, &dsum->parts, s))) return st;
-    hipLaunchKernelGGL(split_fill_kernel, dim3(grid_n), dim3(kThreads), 0, s, cnt, off, n, p->parts,
-                       static_cast<uint32_t>(max_parts));
+                       n, pptr_u, hist, nblocks, dsum);
+    if ((st = exclusive_scan(pptr_u, static_cast<int64_t>(n) + 1, scan_sums, s))) return st;
+    // the schedule's tiles are the sort's: kThreads * sort_items rows
+    auto schedule = [&](auto items) {
+        constexpr int ITEMS = decltype(items)::value;
+        hipLaunchKernelGGL(schedule_count_kernel<ITEMS>, dim3(nblocks), dim3(kThreads), 0, s, p->pptr, n,
+                           p->dense_chunk, dsum, cnt, tile_sums);
+        if (nblocks > kDirectTiles)
+            hipLaunchKernelGGL(schedule_top_kernel, dim3(1), dim3(kThreads), 0, s, tile_sums, nblocks);
+        hipLaunchKernelGGL(schedule_fill_kernel<ITEMS>, dim3(nblocks), dim3(kThreads), 0, s, p->pptr, n, dsum, cnt,
+                           tile_sums, p->tasks, p->parts, static_cast<uint32_t>(max_parts), copy_tile, p->tile_row,
+                           nblocks > kDirectTiles ? 1 : 0);
+    };
+    if (sort_items == kItems) schedule(std::integral_constant<int, kItems>());
+    else schedule(std::integral_constant<int, kSortItemsSmall>());
     if ((st = hip_status(hipGetLastError()))) return st;
     // the schedule sizes are read back while the sorted copy, the last kernel and the only
     // one after them, runs: it reads the plan and the caller's matrix, not the scratch block
@@ -1406,11 +1452,14 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
         }
     }
     if (nnz > 0) {
-        const unsigned grid_e = static_cast<unsigned>((nnz + kCopyTile - 1) / kCopyTile);
-        hipLaunchKernelGGL(tile_row_kernel, dim3(grid_n), dim3(kThreads), 0, s, p->pptr, n, p->tile_row);
-        hipLaunchKernelGGL(sorted_copy_kernel, dim3(grid_e), dim3(kThreads), 0, s, p->order,
-                           csr->rowptr, marked ? marked : csr->col, csr->val, p->pptr, p->tile_row,
-                           n, nnz, p->pcol, p->pval);
+        const unsigned grid_e = static_cast<unsigned>((nnz + copy_tile - 1) / copy_tile);
+        const int32_t *cols = marked ? marked : csr->col;
+        if (copy_tile == kCopyTileSmall)
+            hipLaunchKernelGGL(sorted_copy_kernel<kCopyTileSmall>, dim3(grid_e), dim3(kThreads), 0, s, p->order,
+                               csr->rowptr, cols, csr->val, p->pptr, p->tile_row, n, nnz, p->pcol, p->pval);
+        else
+            hipLaunchKernelGGL(sorted_copy_kernel<kCopyTile>, dim3(grid_e), dim3(kThreads), 0, s, p->order,
+                               csr->rowptr, cols, csr->val, p->pptr, p->tile_row, n, nnz, p->pcol, p->pval);
         if ((st = hip_status(hipGetLastError()))) return st;
     }
     // every use of the plan's sorted copy waits for this event (its stream, or any other)
