@@ -24,7 +24,8 @@
 // lines at F = 128, 32 lanes).  Features beyond 256 are processed in windows of
 // 256; a window may be cut into S slices, workgroup b working on slice b % S (64 features
 // each where rows are whole lines, so that each XCD reads its own slices: sliced_window;
-// also the one-feature-per-lane path for arbitrary F).
+// also the one-feature-per-lane path for F < 4).  Rows may start anywhere: a width that is no
+// multiple of four lets its last lane overlap its neighbour (lane_feature).
 //
 // Gathers.  A group takes the entries of its row (or task) in rounds of 16:
 // each lane loads 16 / LPR (column, value) pairs with coalesced loads, the
@@ -71,13 +72,16 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kRound = 16;            // entries a lane group adds per round
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// rows of any width start at any multiple of 4 (or, in bfloat16, 2) bytes
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32_any __attribute__((aligned(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
 template <int VEC>
 __device__ __forceinline__ void load_x(const float *__restrict__ p, float (&x)[VEC]) {
     if constexpr (VEC == 4) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(p);
+        const f32x4_any v = *reinterpret_cast<const f32x4_any *>(p);
         x[0] = v[0];
         x[1] = v[1];
         x[2] = v[2];
@@ -104,8 +108,8 @@ __device__ __forceinline__ void store_y(void *__restrict__ Y, int64_t at, const 
         if constexpr (VEC == 4) {
             const uint2 v = make_uint2(static_cast<uint32_t>(to_bf16(o[0])) | (static_cast<uint32_t>(to_bf16(o[1])) << 16),
                                        static_cast<uint32_t>(to_bf16(o[2])) | (static_cast<uint32_t>(to_bf16(o[3])) << 16));
-            __builtin_nontemporal_store(v.x, reinterpret_cast<uint32_t *>(p));
-            __builtin_nontemporal_store(v.y, reinterpret_cast<uint32_t *>(p) + 1);
+            __builtin_nontemporal_store(v.x, reinterpret_cast<u32_any *>(p));
+            __builtin_nontemporal_store(v.y, reinterpret_cast<u32_any *>(p) + 1);
         } else {
 #pragma unroll
             for (int j = 0; j < VEC; ++j) __builtin_nontemporal_store(to_bf16(o[j]), p + j);
@@ -113,8 +117,8 @@ __device__ __forceinline__ void store_y(void *__restrict__ Y, int64_t at, const 
     } else {
         float *p = static_cast<float *>(Y) + at;
         if constexpr (VEC == 4) {
-            const f32x4 v = {o[0], o[1], o[2], o[3]};
-            __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
+            const f32x4_any v = {o[0], o[1], o[2], o[3]};
+            __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any *>(p));
         } else {
 #pragma unroll
             for (int j = 0; j < VEC; ++j) __builtin_nontemporal_store(o[j], p + j);
@@ -140,6 +144,7 @@ struct Args {
     int32_t ld;                 // leading dimension of X and Y (= F)
     int32_t f0;                 // first feature of this launch window
     int32_t fend;               // end of the valid features of the window
+    int32_t fcap;               // last feature a lane's four may start at (see lane_feature)
     int32_t S;                  // feature slices in the window
     int32_t sw;                 // features per slice (at most those of a lane group)
     int32_t nb_parts;           // logical workgroups of hub-row parts
@@ -148,6 +153,14 @@ struct Args {
     int32_t nb_dense;           // nb_long + those of the other dense rows (a group each)
     int32_t relu;
 };
+
+// First of a lane's VEC features, for the lane at position `pos` of the window.  Rows whose width
+// is no multiple of four end inside a lane's four: that lane takes the row's last four instead
+// (F >= 4), the first of which its neighbour computes and stores as well, to the same bits.
+template <int VEC>
+__device__ __forceinline__ int32_t lane_feature(const Args &a, int32_t pos) {
+    return VEC == 4 ? min(a.f0 + pos, a.fcap) : a.f0 + pos;
+}
 
 // Where a finished row goes.  Rows are emitted by whole lane groups (every lane of
 // the group calls row() with the same arguments except its features): `slot` numbers
@@ -232,9 +245,9 @@ enum GatherMode { kBuffer = 0, kClasses = 1, kWide = 2, kHalves = 3 };
 // 9160 / 8968; classes in 16-lane groups keep five: n = 2^21, F = 128 3309 / 3376).
 constexpr unsigned kFourGroupsLds = 38 * 1024;
 
-// Offset of an entry that reads nothing: past the end of every buffer, also with a lane's
-// offset inside a window (below 1 KiB) added, so that a buffer load of it returns zeros.
-constexpr uint32_t kNoEntry = 0xFFFFF000u;
+// Offset of an entry that reads nothing: past the end of every buffer, also with a feature's
+// offset (below 4 MiB) added, so that a buffer load of it returns zeros.
+constexpr uint32_t kNoEntry = 0xFF800000u;
 constexpr uint64_t kMaxBufferBytes = kNoEntry;
 constexpr uint32_t kNoRow = 0x80000000u;        // marks an invalid entry's row in kWide
 
@@ -312,16 +325,15 @@ __device__ __forceinline__ void gather(const Args &a, const Round<LPR, MODE> &r,
             as[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(r.v[(U0 + u) / LPR])));
             // an invalid entry reads the row of the last one and drops it
             const bool ok = (row & kNoRow) == 0;
-            load_x<VEC>(a.X + static_cast<int64_t>(row & kRowMask) * a.ld + (fin ? f : a.f0), xs[u]);
+            load_x<VEC>(a.X + static_cast<int64_t>(row & kRowMask) * a.ld + (fin ? f : 0), xs[u]);
 #pragma unroll
             for (int j = 0; j < VEC; ++j) xs[u][j] = ok ? xs[u][j] : 0.f;
         }
     } else {
-        // the window's first feature is the buffer's start; a lane without features of its
-        // own reads the window's first ones, which nothing uses
+        // a lane without features of its own reads the row's first ones, which nothing uses
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(a.X) + a.f0, 0, static_cast<int>(a.x_bytes - static_cast<uint32_t>(a.f0) * 4u), 0x00020000);
-        const uint32_t lane_off = fin ? static_cast<uint32_t>(f - a.f0) * 4u : 0u;
+            const_cast<float *>(a.X), 0, static_cast<int>(a.x_bytes), 0x00020000);
+        const uint32_t lane_off = fin ? static_cast<uint32_t>(f) * 4u : 0u;
 #pragma unroll
         for (int u = 0; u < Q; ++u) {
             const int src = base4 + ((U0 + u) % LPR) * 4;
@@ -474,8 +486,9 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
     const int li = lane % LPR;
     const int gw = lane / LPR;
     const int gbase = lane - li;
-    const int f = a.f0 + slice * a.sw + li * VEC;
-    const bool fin = li * VEC < a.sw && f < a.fend;
+    const int pos = slice * a.sw + li * VEC;      // the lane's features inside the window
+    const bool fin = li * VEC < a.sw && a.f0 + pos < a.fend;
+    const int f = lane_feature<VEC>(a, pos);
 
     if (lb >= a.nb_parts + a.nb_long && lb < a.nb_parts + a.nb_dense) {
         // ---------------- dense path, shorter rows: one lane group per row
@@ -537,7 +550,7 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
         }
         // a part of a split row: its float64 partial, summed by combine_kernel after this launch
         if (gw == 0 && fin) {
-            double *pp = a.partials + static_cast<int64_t>(first + part) * kMaxSlice + (f - a.f0);
+            double *pp = a.partials + static_cast<int64_t>(first + part) * kMaxSlice + pos;
 #pragma unroll
             for (int j = 0; j < VEC; ++j) pp[j] = tot[j];
         }
@@ -621,8 +634,8 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const Args a) {
     const SplitPart sp = a.parts[blockIdx.x];
     if (sp.part != 0) return;
     const int t = static_cast<int>(threadIdx.x);
-    const int f = a.f0 + t;
-    if (f >= a.fend) return;
+    const int f = lane_feature<4>(a, t & ~3) + (t & 3);       // fcap keeps nothing back where VEC is 1
+    if (a.f0 + (t & ~3) >= a.fend || f >= a.ld) return;
     const double *pp = a.partials + static_cast<int64_t>(sp.first) * kMaxSlice + t;
     double s[1] = {0.0};
     for (int q = 0; q < sp.nparts; ++q) s[0] += pp[static_cast<int64_t>(q) * kMaxSlice];
@@ -1021,6 +1034,7 @@ int launch_spmm_xw(const Plan &p, const float *X, const float *W, float *T, void
     Args a = plan_args(p, X, H, F_in, relu);
     a.f0 = 0;
     a.fend = F_in;
+    a.fcap = F_in - 4;
     a.S = 1;
     a.sw = F_in;
     const int lpr = window_lpr(F_in);
@@ -1047,8 +1061,13 @@ int launch_spmm(const Plan &p, const float *X, void *Y, int32_t F, bool relu, bo
     if (const int st = after_plan(p, s)) return st;
     Args a = plan_args(p, X, Y, F, relu);
 
-    const bool vec = (reinterpret_cast<uintptr_t>(X) % 16 == 0) &&
-                     (reinterpret_cast<uintptr_t>(Y) % (bf ? 8 : 16) == 0) && (F % 4 == 0);
+    // Four features per lane from F = 4 on, whatever the rows' alignment: loads and stores of 16
+    // bytes need only that of a float (bfloat16 stores are split).  With one feature per lane and
+    // groups of 64 an odd width ran at a quarter of it: n = 200,003 (3.4M entries), F = 47
+    // 99 us, as 12 lanes of 16 83; block model n = 2^18 (18.8M entries), F = 47 424 -> 205, F = 7
+    // 420 -> 152.
+    const bool vec = F >= 4;
+    a.fcap = vec ? F - 4 : 0x7FFFFFFF - 4;
     int st = DUALGCN_OK;
     for (int32_t f0 = 0; f0 < F && !st; f0 += kMaxSlice) {
         const int32_t w = F - f0 < kMaxSlice ? F - f0 : kMaxSlice;
@@ -1072,7 +1091,7 @@ int launch_spmm(const Plan &p, const float *X, void *Y, int32_t F, bool relu, bo
             else if (lpr == 32) st = launch_window<32, 4>(a, mode, bf, s);
             else st = launch_window<64, 4>(a, mode, bf, s);
         } else {
-            // any other width or alignment: one feature per lane, 64-feature slices
+            // F < 4: one feature per lane
             a.sw = 64;
             a.S = (w + 63) / 64;
             const int mode = gather_mode(p, F, w, false, a);

@@ -256,3 +256,26 @@ def test_long_rows_shared_by_a_workgroup(dg, device, extra, F_in, F_out):
     torch.cuda.synchronize()
     assert st == dg.OK
     assert torch.equal(T, T2)
+
+
+@pytest.mark.parametrize("F", [1, 3, 4, 5, 7, 33, 47, 50, 63, 65, 127, 130, 255, 257, 258, 261, 514])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_odd_widths_and_unaligned_rows(dg, device, F, shift):
+    """Widths that are no multiple of four and operands that start at any float: every path of
+    the SpMM (sparse tasks, groups, shared and split rows, windows of 256 and less than four
+    features), float32 and bfloat16 outputs, and nothing written outside Y."""
+    g = _long_rows(4)
+    X = dense.features_normal(g.n, F, seed=F, stream_id=41)
+    plan = dg.Plan(*to_dev(g, device), seed=1, walks_per_node=4, walk_len=3)
+    buf = torch.empty(g.n * F + 8, dtype=torch.float32, device=device)
+    Xd = buf[shift:shift + g.n * F].view(g.n, F)
+    Xd.copy_(torch.from_numpy(X))
+    Yr, B = oracle.spmm(g, X)
+    for dt, u in ((torch.float32, 0.0), (torch.bfloat16, 2.0 ** -8)):
+        out = torch.full((g.n * F + 16,), 7.0, dtype=dt, device=device)
+        Yd = out[shift:shift + g.n * F].view(g.n, F)
+        dg.spmm(plan, Xd, Yd, out_bf16=dt == torch.bfloat16)
+        Y = Yd.cpu().to(torch.float64).numpy()
+        # the sum's bound, and a bfloat16 store's half unit in the last place
+        assert np.all(np.abs(Y - Yr) <= 1e-5 * B * (1 + u) + u * np.abs(Yr))
+        assert torch.all(out[:shift] == 7.0) and torch.all(out[shift + g.n * F:] == 7.0)
