@@ -159,8 +159,8 @@ __device__ __forceinline__ void walk_lockstep(const int2 *__restrict__ nodeinfo,
     }
 }
 
-// The same lockstep walks over successor records: succ[e] = (first entry, degree) of
-// the node in column e, so one 8-byte read per step yields the next node together with
+// The same lockstep walks over successor records: record e = (first entry, degree) of
+// the node in column e, so one read per step yields the next node together with
 // what the step after it needs -- one dependent random read per step instead of two.
 // A node is identified by its first entry, which is unique among nodes with entries;
 // a node without entries (it shares its first entry with the next node that has some)
@@ -170,9 +170,40 @@ __device__ __forceinline__ int32_t node_key(int2 rec) {
     return rec.y > 0 ? rec.x : static_cast<int32_t>(static_cast<uint32_t>(rec.x) | 0x80000000u);
 }
 
-template <int MAXD, int WPL>
+// Successor records as a walk reads them.  WideRecords: (first entry, degree), 8 bytes, keyed
+// as above.  PackedRecords: 4 bytes, the first entry in the low `shift` bits and the degree
+// above; a degree that does not fit there reads as all ones, and the low bits then hold the
+// node, whose (first entry, degree) comes from nodeinfo.  The record itself is the key: equal
+// for equal nodes, distinct for any two that one walk can visit (an empty node has degree 0).
+struct WideRecords {
+    const int2 *succ;
+    __device__ __forceinline__ int2 read(int32_t e, int32_t *key) const {
+        const int2 r = succ[e];
+        *key = node_key(r);
+        return r;
+    }
+    __device__ __forceinline__ int32_t key_of(uint32_t, int2 info) const { return node_key(info); }
+};
+
+struct PackedRecords {
+    const uint32_t *succ;
+    const int2 *nodeinfo;
+    uint32_t shift;
+    __device__ __forceinline__ int2 read(int32_t e, int32_t *key) const {
+        const uint32_t r = succ[e];
+        *key = static_cast<int32_t>(r);
+        const uint32_t low = r & ((1u << shift) - 1u), deg = r >> shift;
+        if (deg == (~0u >> shift)) return nodeinfo[low];
+        return make_int2(static_cast<int32_t>(low), static_cast<int32_t>(deg));
+    }
+    __device__ __forceinline__ int32_t key_of(uint32_t v, int2 info) const {
+        return static_cast<int32_t>(pack_record(v, info, shift));
+    }
+};
+
+template <int MAXD, int WPL, class Records>
 __device__ __forceinline__ void walk_lockstep_succ(const int2 *__restrict__ nodeinfo,
-                                                   const int2 *__restrict__ succ, uint32_t v,
+                                                   const Records &rec, uint32_t v,
                                                    uint32_t w0, uint32_t nw, uint32_t d,
                                                    uint64_t seed, uint32_t (&u)[WPL]) {
     int32_t path[WPL][MAXD + 1];
@@ -182,7 +213,7 @@ __device__ __forceinline__ void walk_lockstep_succ(const int2 *__restrict__ node
     const int2 start = nodeinfo[v];
 #pragma unroll
     for (int j = 0; j < WPL; ++j) {
-        path[j][0] = node_key(start);
+        path[j][0] = rec.key_of(v, start);
         cur[j] = start;
         live[j] = static_cast<uint32_t>(j) < nw;
         u[j] = live[j] ? 1 : 0;
@@ -191,26 +222,27 @@ __device__ __forceinline__ void walk_lockstep_succ(const int2 *__restrict__ node
     for (int s = 0; s < MAXD; ++s) {
         if (static_cast<uint32_t>(s) >= d) break;
         int2 nxt[WPL];
+        int32_t key[WPL];
 #pragma unroll
         for (int j = 0; j < WPL; ++j) {
             nxt[j] = cur[j];
+            key[j] = path[j][s];
             if (live[j] && cur[j].y > 0) {
                 if ((s & 7) == 0) blk[j] = philox4x64_10(v, w0 + j, static_cast<uint64_t>(s >> 3), 0, seed, 0);
                 const uint32_t r = half_word(blk[j], s);
-                nxt[j] = succ[cur[j].x + static_cast<int32_t>(__umulhi(r, static_cast<uint32_t>(cur[j].y)))];
+                nxt[j] = rec.read(cur[j].x + static_cast<int32_t>(__umulhi(r, static_cast<uint32_t>(cur[j].y))), &key[j]);
             }
         }
 #pragma unroll
         for (int j = 0; j < WPL; ++j) {
-            const int32_t key = node_key(nxt[j]);
             if (live[j]) {
                 bool seen = false;
 #pragma unroll MAXD
-                for (int i = 0; i <= s; ++i) seen |= path[j][i] == key;
+                for (int i = 0; i <= s; ++i) seen |= path[j][i] == key[j];
                 if (!seen) ++u[j];
-                live[j] = !(cur[j].y <= 1 && key == path[j][s]);   // absorbed: stays put for good
+                live[j] = !(cur[j].y <= 1 && key[j] == path[j][s]);   // absorbed: stays put for good
             }
-            path[j][s + 1] = key;
+            path[j][s + 1] = key[j];
             cur[j] = nxt[j];
         }
     }
@@ -255,10 +287,11 @@ __global__ __launch_bounds__(256) void arw_kernel(const int32_t *__restrict__ ro
 // wavefront: their counts are summed with shuffles and stored once.  Otherwise the
 // counts are summed per node inside the wavefront (a segmented scan) and the node's
 // last lane in the wavefront adds the sum to S[v], which starts at zero.
+// succ: null (columns and node records), WideRecords, or PackedRecords when shift > 0.
 template <int MAXD>
 __global__ __launch_bounds__(256) void arw_sum_kernel(const int2 *__restrict__ nodeinfo,
                                                       const int32_t *__restrict__ col,
-                                                      const int2 *__restrict__ succ,
+                                                      const void *__restrict__ succ, uint32_t shift,
                                                       int32_t n, uint64_t seed, uint32_t k,
                                                       uint32_t d, uint32_t L, int L_log2,
                                                       uint32_t *__restrict__ S,
@@ -280,8 +313,12 @@ __global__ __launch_bounds__(256) void arw_sum_kernel(const int2 *__restrict__ n
     if (valid) {
         const uint32_t nw = k - w0 >= 2 ? 2 : 1;
         uint32_t uj[2];
-        if (succ)
-            walk_lockstep_succ<MAXD, 2>(nodeinfo, succ, v, w0, nw, d, seed, uj);
+        if (shift)
+            walk_lockstep_succ<MAXD, 2>(nodeinfo, PackedRecords{static_cast<const uint32_t *>(succ), nodeinfo, shift},
+                                        v, w0, nw, d, seed, uj);
+        else if (succ)
+            walk_lockstep_succ<MAXD, 2>(nodeinfo, WideRecords{static_cast<const int2 *>(succ)}, v, w0, nw, d, seed,
+                                        uj);
         else
             walk_lockstep<MAXD, 2>(nodeinfo, col, v, w0, nw, d, seed, uj);
         u = uj[0] + uj[1];
@@ -302,7 +339,7 @@ __global__ __launch_bounds__(256) void arw_sum_kernel(const int2 *__restrict__ n
 
 }  // namespace
 
-int launch_density(const int2 *nodeinfo, const int32_t *col, const int2 *succ, int32_t n,
+int launch_density(const int2 *nodeinfo, const int32_t *col, const void *succ, uint32_t shift, int32_t n,
                    uint64_t seed, uint32_t k, uint32_t d, uint32_t *S, const int32_t *bad_flag,
                    hipStream_t stream) {
     if (d > 32 || k < 1) return DUALGCN_ERR_UNSUPPORTED;
@@ -320,11 +357,11 @@ int launch_density(const int2 *nodeinfo, const int32_t *col, const int2 *succ, i
     }
     const dim3 grid(static_cast<unsigned>(blocks)), block(256);
     if (d <= 8)
-        hipLaunchKernelGGL((arw_sum_kernel<8>), grid, block, 0, stream, nodeinfo, col, succ, n, seed,
-                           k, d, L, L_log2, S, bad_flag);
+        hipLaunchKernelGGL((arw_sum_kernel<8>), grid, block, 0, stream, nodeinfo, col, succ, shift,
+                           n, seed, k, d, L, L_log2, S, bad_flag);
     else
-        hipLaunchKernelGGL((arw_sum_kernel<32>), grid, block, 0, stream, nodeinfo, col, succ, n,
-                           seed, k, d, L, L_log2, S, bad_flag);
+        hipLaunchKernelGGL((arw_sum_kernel<32>), grid, block, 0, stream, nodeinfo, col, succ,
+                           shift, n, seed, k, d, L, L_log2, S, bad_flag);
     return hip_status(hipGetLastError());
 }
 

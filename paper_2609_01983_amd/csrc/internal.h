@@ -166,10 +166,15 @@ int launch_arw(const int32_t *rowptr, const int32_t *col, int32_t n, uint64_t se
                uint32_t d, uint32_t *S, uint8_t *patterns, const int32_t *bad_flag,
                hipStream_t stream);
 // The same sums from nodeinfo (every node's (first entry, degree), as validate_csr writes
-// it), two walks per lane advanced in lockstep.  With succ (succ[e] = (first entry, degree)
-// of the node in column e) each step reads one record instead of a node's bounds and then
+// it), two walks per lane advanced in lockstep.  With succ (record e = (first entry, degree)
+// of the node in column e: int2, or with shift > 0 pack_record's 4 bytes) each step reads one record instead of a node's bounds and then
 // a column.  DUALGCN_ERR_UNSUPPORTED (nothing launched) when d > 32.
-int launch_density(const int2 *nodeinfo, const int32_t *col, const int2 *succ, int32_t n,
+__host__ __device__ inline uint32_t pack_record(uint32_t node, int2 info, uint32_t shift) {
+    const uint32_t all = ~0u >> shift;                    // the largest degree field: look the node up
+    const uint32_t deg = static_cast<uint32_t>(info.y);
+    return deg < all ? (deg << shift) | static_cast<uint32_t>(info.x) : (all << shift) | node;
+}
+int launch_density(const int2 *nodeinfo, const int32_t *col, const void *succ, uint32_t shift, int32_t n,
                    uint64_t seed, uint32_t k, uint32_t d, uint32_t *S, const int32_t *bad_flag,
                    hipStream_t stream);
 

@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kThreads) void validate_kernel(const int32_t *__res
 __global__ __launch_bounds__(kThreads) void successor_kernel(const int2 *__restrict__ nodeinfo,
                                                              const int32_t *__restrict__ col,
                                                              int32_t n, int64_t nnz,
-                                                             int2 *__restrict__ succ,
+                                                             void *__restrict__ succ, uint32_t shift,
                                                              const uint32_t *__restrict__ hot_heat,
                                                              int32_t *__restrict__ marked,
                                                              int32_t *__restrict__ flag) {
@@ -144,7 +144,8 @@ __global__ __launch_bounds__(kThreads) void successor_kernel(const int2 *__restr
         const bool in = c >= 0 && c < n;
         if (!in) atomicOr(flag, 2);
         const int2 r = in ? nodeinfo[c] : make_int2(0, 0);
-        if (succ) succ[e] = r;
+        if (succ && shift) static_cast<uint32_t *>(succ)[e] = in ? pack_record(static_cast<uint32_t>(c), r, shift) : 0u;
+        else if (succ) static_cast<int2 *>(succ)[e] = r;
         if (marked) {
             const bool cold = heat_of(static_cast<uint32_t>(r.y)) < hot;
             marked[e] = static_cast<int32_t>(static_cast<uint32_t>(c) | (cold ? 0x80000000u : 0u));
@@ -1171,6 +1172,16 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
     // costs one random read per entry and saves one dependent random read per step.
     const bool use_succ = S_host == nullptr &&
                           static_cast<u128>(n) * k * d >= 2 * static_cast<u128>(unnz);
+    // Records of 4 bytes where a degree below 2^(32 - shift) - 1 fits above the first entry (and
+    // the node id) and leaves at least kPackedDegreeBits of them: the few nodes of higher degree
+    // are read from their node records, which stay in the caches.  Half the bytes to walk over:
+    // walk kernel, 1.2M entries, 50 walks of 30 steps 468 -> 286 us, 1.3M entries, 16 of 5 40.5
+    // -> 30.3.  With fewer bits too many steps of a power-law graph land on a node that does not
+    // fit.  Plans of 50 x 30 walks, wide / packed (us): 4.2M entries (9 bits) 3358 / 2788, 8.4M
+    // (8 bits) 6990 / 6614, 16.8M (7 bits) 13830 / 16308.
+    constexpr uint32_t kPackedDegreeBits = 8;
+    const uint32_t first_bits = static_cast<uint32_t>(std::max(bit_length(static_cast<uint64_t>(nnz)), bit_length(static_cast<uint64_t>(n))));
+    const uint32_t succ_shift = use_succ && first_bits + kPackedDegreeBits <= 32 ? first_bits : 0;
     // columns outside the hottest kHotRows are marked (bit 31 of the sorted copy's columns)
     // for the cache classes of the gathers, only when a launch on the plan can use them
     // (an operand of rows up to kMaxSlice floats larger than kGatherClassMinBytes): the
@@ -1203,7 +1214,7 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
                  o_ssum = ls.take(sizeof(SplitSummary)), o_counts = ls.take(sizeof(uint32_t) * un),
                  o_tsums = ls.take(sizeof(uint64_t) * static_cast<size_t>(nblocks)),
                  o_info = ls.take(sizeof(int2) * un),
-                 o_succ = ls.take(use_succ ? sizeof(int2) * unnz : 0),
+                 o_succ = ls.take(use_succ ? (succ_shift ? sizeof(uint32_t) : sizeof(int2)) * unnz : 0),
                  o_marked = ls.take(mark ? sizeof(int32_t) * unnz : 0),
                  o_bmax = ls.take(sizeof(int32_t) * kValidateBlocks);
     if ((st = alloc_block(&p->mem, &p->mem_bytes, lp.bytes))) return st;
@@ -1267,12 +1278,12 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
     if ((st = validate_csr(csr, bad, nodeinfo, blockmax, mark ? heat_hist : nullptr, s, !succ_pass)))
         return st;
     if (mark) hipLaunchKernelGGL(hot_heat_kernel, dim3(1), dim3(kHeatLevels), 0, s, heat_hist, kHotRows, hot_heat);
-    int2 *succ = nullptr;
+    void *succ = nullptr;
     if (succ_pass) {
-        if (use_succ) succ = reinterpret_cast<int2 *>(sm + o_succ);
+        if (use_succ) succ = sm + o_succ;
         const int64_t sblocks = std::min<int64_t>((nnz + kThreads - 1) / kThreads, 65536);
         hipLaunchKernelGGL(successor_kernel, dim3(static_cast<unsigned>(sblocks)), dim3(kThreads), 0,
-                           s, nodeinfo, csr->col, n, nnz, succ, hot_heat, marked, bad);
+                           s, nodeinfo, csr->col, n, nnz, succ, succ_shift, hot_heat, marked, bad);
     }
     if (S_host) {
         // the density sums of a saved plan of this matrix: no walks
@@ -1281,7 +1292,7 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
             return st;
     } else {
         // walks: the lockstep walker where it applies, else one walk per lane
-        st = launch_density(nodeinfo, csr->col, succ, n, seed, k, d, p->S, bad, s);
+        st = launch_density(nodeinfo, csr->col, succ, succ ? succ_shift : 0, n, seed, k, d, p->S, bad, s);
         if (st == DUALGCN_ERR_UNSUPPORTED)
             st = launch_arw(csr->rowptr, csr->col, n, seed, k, d, p->S, nullptr, bad, s);
         if (st) return st;

@@ -511,3 +511,31 @@ def test_destroy_waits_for_launches_on_other_streams(dg, device):
         for Y in Ys:
             assert torch.equal(Y, Y_ref)
         other.destroy()
+
+
+@pytest.mark.parametrize("m", [(1 << 23) - 1, 1 << 23, (1 << 24) - 1, 1 << 24])
+def test_walk_records_of_four_and_eight_bytes(dg, device, m):
+    """Density sums on both sides of the packed records' bounds: the degree field has 9 bits
+    (255 and more are looked up) below 2^23 entries, 8 bits below 2^24, and from there the
+    records take 8 bytes.  Rows of 0, 1, 254 to 256, 510 to 512 and a few thousand entries."""
+    from graphgen.csr import Graph
+    gen = np.random.default_rng(m)
+    n = 60001
+    want = gen.choice([0, 1, 2, 30, 254, 255, 256, 510, 511, 512, 700], size=n).astype(np.int64)
+    want[gen.integers(0, n, 5)] = 4000
+    want = np.minimum(want, np.maximum(0, m - np.concatenate([[0], np.cumsum(want)[:-1]])))
+    short = m - int(want.sum())
+    want += short // n
+    want[: short % n] += 1
+    assert int(want.sum()) == m
+    rowptr = np.zeros(n + 1, dtype=np.int32)
+    rowptr[1:] = np.cumsum(want)
+    g = Graph(n=n, rowptr=rowptr, col=gen.integers(0, n, m).astype(np.int32),
+              val=np.ones(m, dtype=np.float32))
+    k, d = 40, 16                      # at least twice as many steps as entries
+    assert n * k * d >= 2 * m
+    plan = dg.Plan(*to_dev(g, device), seed=7, walks_per_node=k, walk_len=d)
+    _, S, _ = plan.export()
+    pat = dg.arw_patterns(*to_dev(g, device), 7, k, d)     # one walk per lane on the row pointers
+    ref = pat.amax(dim=2).to(torch.int64).sum(dim=1).cpu().numpy()
+    assert np.array_equal(S.astype(np.int64), ref)
