@@ -199,8 +199,10 @@ __global__ __launch_bounds__(kThreads) void checksum_kernel(const int32_t *__res
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     const int64_t t0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     uint64_t acc = 0;
+#pragma unroll 4
     for (int64_t i = t0; i <= n; i += stride)
         acc += mix64((static_cast<uint64_t>(i) << 32) ^ static_cast<uint32_t>(rowptr[i]));
+#pragma unroll 8
     for (int64_t e = t0; e < nnz; e += stride)
         acc += mix64(((static_cast<uint64_t>(e) << 32) ^ static_cast<uint32_t>(col[e])) +
                      0x9E3779B97F4A7C15ull);
@@ -214,11 +216,18 @@ __global__ __launch_bounds__(kThreads) void checksum_kernel(const int32_t *__res
     if (t == 0) partial[blockIdx.x] = sh[0];
 }
 
-__global__ void checksum_fold_kernel(uint64_t *__restrict__ partial) {
+// partial[kSumBlocks] = the sum of the others (one workgroup; one thread took 16 us).
+__global__ __launch_bounds__(kThreads) void checksum_fold_kernel(uint64_t *__restrict__ partial) {
+    __shared__ uint64_t shw[kThreads / 64];
     uint64_t s = 0;
-    for (int i = 0; i < kSumBlocks; ++i) s += partial[i];
-    partial[kSumBlocks] = s;
+#pragma unroll
+    for (int i = 0; i < kSumBlocks / kThreads; ++i) s += partial[i * kThreads + threadIdx.x];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((threadIdx.x & 63) == 0) shw[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) partial[kSumBlocks] = shw[0] + shw[1] + shw[2] + shw[3];
 }
+static_assert(kThreads == 256 && kSumBlocks % kThreads == 0, "four wavefronts, whole rounds");
 
 // ------------------------------------------------------------------ keys and moments
 
@@ -453,9 +462,10 @@ __global__ __launch_bounds__(kThreads) void scan_apply_kernel(const uint32_t *in
 
 // Sort tiles hold kThreads * ITEMS keys: 16 per thread on large inputs, 4 below
 // kSortSmallKeys keys, where 4096-key tiles would leave most CUs idle and make every
-// wavefront walk 16 rounds in a row (c2, 2^17 keys: 32 workgroups).
+// wavefront walk 16 rounds in a row (c2, 2^17 keys: 32 workgroups).  Whole plans with 16 / 4
+// keys per thread: n = 2^20 1062 / 1030 us, n = 2^21 2651 / 2624.
 constexpr int kSortItemsSmall = 4;
-constexpr int64_t kSortSmallKeys = int64_t{1} << 20;
+constexpr int64_t kSortSmallKeys = int64_t{1} << 23;
 
 template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void radix_hist_kernel(const uint64_t *__restrict__ keys,
@@ -1125,7 +1135,7 @@ int structure_checksum(const int32_t *rowptr, const int32_t *col, int32_t n, int
     uint64_t *partial = static_cast<uint64_t *>(buf);
     hipLaunchKernelGGL(checksum_kernel, dim3(kSumBlocks), dim3(kThreads), 0, s, rowptr, col, n, nnz,
                        partial);
-    hipLaunchKernelGGL(checksum_fold_kernel, dim3(1), dim3(1), 0, s, partial);
+    hipLaunchKernelGGL(checksum_fold_kernel, dim3(1), dim3(kThreads), 0, s, partial);
     st = hip_status(hipGetLastError());
     if (!st) st = hip_status(hipMemcpyAsync(out, partial + kSumBlocks, sizeof(uint64_t),
                                             hipMemcpyDeviceToHost, s));
@@ -1191,6 +1201,10 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
     const int sort_items = n < kSortSmallKeys ? kSortItemsSmall : kItems;
     const int64_t sort_tile = static_cast<int64_t>(kThreads) * sort_items;
     const int32_t nblocks = static_cast<int32_t>((static_cast<int64_t>(n) + sort_tile - 1) / sort_tile);
+    // schedule tiles of 1,024 rows while the fill can add their sums itself (n = 2^20, tiles of
+    // 4,096 / 1,024 rows: count 19.7 / 9.8 us, fill 19.1 / 8.1; n = 2^21 22.0 / 13.9, 32.3 / 14.3)
+    const int sched_items = n <= kDirectTiles * kThreads * kSortItemsSmall ? kSortItemsSmall : kItems;
+    const int32_t sched_tiles = static_cast<int32_t>((static_cast<int64_t>(n) + kThreads * sched_items - 1) / (kThreads * sched_items));
     const int64_t scan_tiles = std::max((static_cast<int64_t>(kRadix) * nblocks + kTile - 1) / kTile,
                                         (static_cast<int64_t>(n) + 1 + kTile - 1) / kTile) + 1;
     const int32_t copy_tile = nnz < kCopySmallNnz ? kCopyTileSmall : kCopyTile;
@@ -1212,7 +1226,7 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
                  o_scan = ls.take(sizeof(uint32_t) * static_cast<size_t>(scan_tiles)),
                  o_hist = ls.take(sizeof(uint32_t) * kRadix * static_cast<size_t>(nblocks)),
                  o_ssum = ls.take(sizeof(SplitSummary)), o_counts = ls.take(sizeof(uint32_t) * un),
-                 o_tsums = ls.take(sizeof(uint64_t) * static_cast<size_t>(nblocks)),
+                 o_tsums = ls.take(sizeof(uint64_t) * static_cast<size_t>(sched_tiles)),
                  o_info = ls.take(sizeof(int2) * un),
                  o_succ = ls.take(use_succ ? (succ_shift ? sizeof(uint32_t) : sizeof(int2)) * unnz : 0),
                  o_marked = ls.take(mark ? sizeof(int32_t) * unnz : 0),
@@ -1422,18 +1436,17 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
     hipLaunchKernelGGL(sorted_degree_kernel, dim3(grid_n1), dim3(kThreads), 0, s, p->order, csr->rowptr,
                        n, pptr_u, hist, nblocks, dsum);
     if ((st = exclusive_scan(pptr_u, static_cast<int64_t>(n) + 1, scan_sums, s))) return st;
-    // the schedule's tiles are the sort's: kThreads * sort_items rows
     auto schedule = [&](auto items) {
         constexpr int ITEMS = decltype(items)::value;
-        hipLaunchKernelGGL(schedule_count_kernel<ITEMS>, dim3(nblocks), dim3(kThreads), 0, s, p->pptr, n,
+        hipLaunchKernelGGL(schedule_count_kernel<ITEMS>, dim3(sched_tiles), dim3(kThreads), 0, s, p->pptr, n,
                            p->dense_chunk, dsum, cnt, tile_sums);
-        if (nblocks > kDirectTiles)
-            hipLaunchKernelGGL(schedule_top_kernel, dim3(1), dim3(kThreads), 0, s, tile_sums, nblocks);
-        hipLaunchKernelGGL(schedule_fill_kernel<ITEMS>, dim3(nblocks), dim3(kThreads), 0, s, p->pptr, n, dsum, cnt,
+        if (sched_tiles > kDirectTiles)
+            hipLaunchKernelGGL(schedule_top_kernel, dim3(1), dim3(kThreads), 0, s, tile_sums, sched_tiles);
+        hipLaunchKernelGGL(schedule_fill_kernel<ITEMS>, dim3(sched_tiles), dim3(kThreads), 0, s, p->pptr, n, dsum, cnt,
                            tile_sums, p->tasks, p->parts, static_cast<uint32_t>(max_parts), copy_tile, p->tile_row,
-                           nblocks > kDirectTiles ? 1 : 0);
+                           sched_tiles > kDirectTiles ? 1 : 0);
     };
-    if (sort_items == kItems) schedule(std::integral_constant<int, kItems>());
+    if (sched_items == kItems) schedule(std::integral_constant<int, kItems>());
     else schedule(std::integral_constant<int, kSortItemsSmall>());
     if ((st = hip_status(hipGetLastError()))) return st;
     // the schedule sizes are read back while the sorted copy, the last kernel and the only
