@@ -709,10 +709,7 @@ void spmm_xw_kernel(const Args a, const float *__restrict__ W,
     float *stage_own = reinterpret_cast<float *>(reinterpret_cast<int32_t *>(xw_lds + (N + kWaves * ROWS) * ld) +
                                                  kWaves * ROWS) + wave * kXwStageWords;
     __shared__ double red[MODE == kBuffer ? (kWaves - 1) * LPR * 4 : 1];
-    for (int idx = static_cast<int>(threadIdx.x); idx < K * N; idx += kThreads) {
-        const int c = idx / N, j = idx % N;   // consecutive threads read consecutive columns
-        wt[j * ld + c] = to_bf16(W[idx]);
-    }
+    stage_w<kThreads>(wt, ld, W, N, K, N);
     if (lane < ROWS) outs[lane] = -1;
     __syncthreads();
 

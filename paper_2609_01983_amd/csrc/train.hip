@@ -507,6 +507,7 @@ __global__ __launch_bounds__(kTrThreads) void wgrad_tr_kernel(const unsigned sho
 // W[e] -= lr dW[e].  A workgroup covers 32 consecutive elements.
 constexpr int kReduceSegs = 8;
 constexpr int kReduceElems = kThreads / kReduceSegs;
+constexpr int kReduceBatch = 16;
 __global__ __launch_bounds__(kThreads) void wgrad_reduce_kernel(const float *__restrict__ partial,
                                                                 int32_t count, int64_t elems,
                                                                 float *__restrict__ dW, float lr,
@@ -519,8 +520,17 @@ __global__ __launch_bounds__(kThreads) void wgrad_reduce_kernel(const float *__r
         const int64_t e = e0 + el;
         double s = 0.0;
         if (e < elems) {
+            // kReduceBatch partials are requested at a time, and added in order
             const int b1 = min(count, (seg + 1) * per);
-            for (int b = seg * per; b < b1; ++b) s += static_cast<double>(partial[b * elems + e]);
+            int b = seg * per;
+            for (; b + kReduceBatch <= b1; b += kReduceBatch) {
+                float v[kReduceBatch];
+#pragma unroll
+                for (int q = 0; q < kReduceBatch; ++q) v[q] = partial[(b + q) * elems + e];
+#pragma unroll
+                for (int q = 0; q < kReduceBatch; ++q) s += static_cast<double>(v[q]);
+            }
+            for (; b < b1; ++b) s += static_cast<double>(partial[b * elems + e]);
         }
         sh[seg][el] = s;
         __syncthreads();

@@ -132,17 +132,8 @@ __global__ __launch_bounds__(kThreads) void xw_mfma_kernel(const void *__restric
     extern __shared__ unsigned short w_lds[];   // [16 ntiles][K + kPad]: B^T in bf16
     const int ldw = K + kPad;
     const int ncols = 16 * ntiles;
-    if (sn == 1) {          // consecutive threads read consecutive columns of W
-        for (int idx = threadIdx.x; idx < K * ncols; idx += kThreads) {
-            const int c = idx / ncols, j = idx % ncols;
-            w_lds[j * ldw + c] = to_bf16(W[static_cast<int64_t>(c) * sk + c0 + j]);
-        }
-    } else {                // consecutive threads read consecutive k of W's rows
-        for (int idx = threadIdx.x; idx < K * ncols; idx += kThreads) {
-            const int j = idx / K, c = idx % K;
-            w_lds[j * ldw + c] = to_bf16(W[static_cast<int64_t>(c0 + j) * sn + c]);
-        }
-    }
+    if (sn == 1) stage_w<kThreads>(w_lds, ldw, W + c0, sk, K, ncols);
+    else stage_wt<kThreads>(w_lds, ldw, W + static_cast<int64_t>(c0) * sn, sn, K, ncols);
     __syncthreads();
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
