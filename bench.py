@@ -731,6 +731,8 @@ def main():
     ge_per_step = g.nnz * (sum(fo for _, fo in w.layers) if w.is_gcn else w.F)
     value = ge_per_step / (ms_per_step * 1e-3) / 1e9
     lpr = min(64, max(1, 1 << max(0, (F_dom - 1).bit_length() - 2)))
+    if not fused and F_dom > 64 and F_dom % 64 == 0:
+        lpr = 16                              # slices of 64 features
     cp = "true" if gather_classes(info, g.n, F_dom) else "false"
     if fused:
         # the dominant kernel is layer 1's aggregation with layer 2's update fused in: it
