@@ -63,7 +63,10 @@ def _tiles(n, lengths, seed):
 @pytest.mark.parametrize("n,lengths", [
     (1, [1]), (1, [2048]), (1, [2049]), (2, [2048, 1]), (3, [0, 4096, 0]), (700, [0, 0, 0, 7, 0]),
     (5000, [0] * 999 + [3]),        # tiles that meet more rows than entries
-    (4097, [1]), (300, [0, 31, 5000, 1, 2])])
+    (4097, [1]), (300, [0, 31, 5000, 1, 2]),
+    (1 << 18, [1]), ((1 << 18) + 1, [1]),     # the last matrix searched entry by entry, the next
+    (300000, [0, 0, 5, 0, 9, 0]),             # tiles with empty rows
+    (1200000, [0] * 2999 + [1400])])          # tiles that meet more rows than entries
 @pytest.mark.parametrize("kind", ["gcn", "mean", "sum"])
 def test_aggregator_tiles(dg, device, n, lengths, kind):
     """Rows that start, end and span at the edges of the kernel's tiles of 2,048 entries."""
