@@ -4,6 +4,8 @@ Values: float64 arithmetic rounded once to float32 on both sides; they may diffe
 where the device square root is not correctly rounded, so the test allows one float32
 ulp and reports how many values match exactly.  SpMM: the usual 1e-5 sum |a||x| bound.
 """
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -66,6 +68,8 @@ def _tiles(n, lengths, seed):
     (4097, [1]), (300, [0, 31, 5000, 1, 2]),
     (1 << 18, [1]), ((1 << 18) + 1, [1]),     # the last matrix searched entry by entry, the next
     (300000, [0, 0, 5, 0, 9, 0]),             # tiles with empty rows
+    (1, [300000]), (3, [5, 290000, 7]),       # a row of more tiles than its wavefront has lanes
+    (70, [32768, 32769, 3]), (130, [0, 40000]),   # rows on both sides of 16 tiles, several a wavefront
     (1200000, [0] * 2999 + [1400])])          # tiles that meet more rows than entries
 @pytest.mark.parametrize("kind", ["gcn", "mean", "sum"])
 def test_aggregator_tiles(dg, device, n, lengths, kind):
@@ -78,6 +82,33 @@ def test_aggregator_tiles(dg, device, n, lengths, kind):
     finite = np.isfinite(ref)                       # a column whose own row is empty: 1 / 0
     assert np.array_equal(np.isfinite(v), finite)
     assert _ulps(v[finite], ref[finite]).max(initial=0) <= 1
+
+
+def _ms(call):
+    """Shortest of ten calls, each waited for."""
+    best = float("inf")
+    for _ in range(10):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        call()
+        torch.cuda.synchronize()
+        best = min(best, 1e3 * (time.perf_counter() - t))
+    return best
+
+
+def test_one_row_of_all_entries_costs_no_more_than_short_rows(dg, device):
+    """2^24 entries in rows of 64, and all of them in one row of the same nodes: the same bytes.
+    One thread that wrote all tile ends of the row took the call to three times as long."""
+    n, m = 1 << 18, 1 << 24
+    gen = torch.Generator(device=device).manual_seed(3)
+    col = torch.randint(0, n, (m,), device=device, dtype=torch.int32, generator=gen)
+    spread = (torch.arange(n + 1, device=device) * (m // n)).to(torch.int32)
+    one = torch.zeros(n + 1, dtype=torch.int32, device=device)
+    one[n // 3:] = m
+    val = torch.empty(m, dtype=torch.float32, device=device)
+    times = [_ms(lambda: dg.aggregator_values(rp, col, "mean", val=val)) for rp in (spread, one)]
+    assert times[1] <= 1.6 * times[0], times
+    assert torch.all(val == torch.tensor(1.0 / m, dtype=torch.float64).float().item())
 
 
 @pytest.mark.parametrize("kind", ["mean", "sum"])
