@@ -800,7 +800,24 @@ __global__ __launch_bounds__(kThreads) void schedule_top_kernel(uint64_t *__rest
 // tiles of the sorted copy that start inside them: tile_row[t] = the sorted row that holds
 // entry t * copy_tile.  Thread t takes ITEMS consecutive rows.  (Six counting, scanning and
 // filling launches for tasks and parts each, and one for tile_row, before: 1.3M entries, n =
-// 2^17, 13 launches of 2-4 us.)
+// 2^17, 13 launches of 2-4 us.)  A row with more than kOwnSlots tiles or parts is shared by its
+// thread's wavefront: one thread alone writes them one after the other (plan of one row of 7.3M entries
+// 807 us, of 2^30 45.4 ms; shared 210 and 15.7).
+constexpr uint32_t kOwnSlots = 16;
+
+__device__ __forceinline__ bool shared_row(uint32_t m, uint32_t t0, uint32_t t1) {
+    return t1 - t0 > kOwnSlots || m > kOwnSlots;
+}
+
+// Parts first, first + step, ... of row i's m, and likewise its tiles [t0, t1).
+__device__ __forceinline__ void fill_row(int32_t i, uint32_t m, uint32_t part, uint32_t t0, uint32_t t1,
+                                         SplitPart *__restrict__ parts, uint32_t max_parts,
+                                         int32_t *__restrict__ tile_row, uint32_t first, uint32_t step) {
+    for (uint32_t j = first; j < m && part + j < max_parts; j += step)
+        parts[part + j] = SplitPart{i, static_cast<int32_t>(j), static_cast<int32_t>(m), static_cast<int32_t>(part)};
+    for (uint32_t t = t0 + first; t < t1; t += step) tile_row[t] = i;
+}
+
 template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void schedule_fill_kernel(const int32_t *__restrict__ pptr, int32_t n,
                                                                  SplitSummary *__restrict__ sum,
@@ -835,25 +852,42 @@ __global__ __launch_bounds__(kThreads) void schedule_fill_kernel(const int32_t *
     }
     if (lane == 63) shw[wave] = inc;
     __syncthreads();
-    uint64_t at = before + inc - s;
-    for (int w = 0; w < wave; ++w) at += shw[w];
+    uint64_t start = before + inc - s;
+    for (int w = 0; w < wave; ++w) start += shw[w];
+    const uint32_t ct = static_cast<uint32_t>(copy_tile);
+    uint64_t at = start;
+    bool many = false;                        // some row of this thread's is shared
     for (int k = 0; k < ITEMS; ++k) {
         const int64_t i = base + k;
         if (i >= n) break;
-        const uint32_t task = static_cast<uint32_t>(at), part = static_cast<uint32_t>(at >> 32);
+        const uint32_t task = static_cast<uint32_t>(at), part = static_cast<uint32_t>(at >> 32), m = c[k] >> 1;
         if (c[k] & 1u) tasks[task] = static_cast<int32_t>(i);
-        const uint32_t m = c[k] >> 1;
-        for (uint32_t j = 0; j < m && part + j < max_parts; ++j)
-            parts[part + j] = SplitPart{static_cast<int32_t>(i), static_cast<int32_t>(j),
-                                        static_cast<int32_t>(m), static_cast<int32_t>(part)};
         at += (c[k] & 1u) | (static_cast<uint64_t>(m) << 32);
-        const int64_t b = pptr[i], e = pptr[i + 1];
-        for (int64_t t = (b + copy_tile - 1) / copy_tile; t * copy_tile < e; ++t)
-            tile_row[t] = static_cast<int32_t>(i);
+        // the tiles [t0, t1) of the sorted copy start inside the row
+        const uint32_t t0 = (static_cast<uint32_t>(pptr[i]) + ct - 1) / ct;
+        const uint32_t t1 = (static_cast<uint32_t>(pptr[i + 1]) + ct - 1) / ct;
+        if (shared_row(m, t0, t1)) many = true;
+        else fill_row(static_cast<int32_t>(i), m, part, t0, t1, parts, max_parts, tile_row, 0, 1);
         if (i == n - 1) {
             sum->tasks = static_cast<uint32_t>(at);
             sum->parts = static_cast<uint32_t>(at >> 32);
             tasks[static_cast<uint32_t>(at)] = sum->n_sparse;
+        }
+    }
+    if (__ballot(many) == 0) return;
+    at = start;
+#pragma unroll 1
+    for (int k = 0; k < ITEMS; ++k) {
+        const bool in = base + k < n;
+        const int32_t i = in ? static_cast<int32_t>(base + k) : 0;
+        const uint32_t ck = in ? cnt[i] : 0u, part = static_cast<uint32_t>(at >> 32), m = ck >> 1;
+        at += static_cast<uint64_t>(m) << 32;
+        const uint32_t t0 = in ? (static_cast<uint32_t>(pptr[i]) + ct - 1) / ct : 0;
+        const uint32_t t1 = in ? (static_cast<uint32_t>(pptr[i + 1]) + ct - 1) / ct : 0;
+        for (uint64_t rows = __ballot(shared_row(m, t0, t1)); rows != 0; rows &= rows - 1) {
+            const int src = __ffsll(static_cast<unsigned long long>(rows)) - 1;
+            fill_row(__shfl(i, src, 64), __shfl(m, src, 64), __shfl(part, src, 64), __shfl(t0, src, 64),
+                     __shfl(t1, src, 64), parts, max_parts, tile_row, static_cast<uint32_t>(lane), 64);
         }
     }
 }

@@ -4,6 +4,8 @@
 * SpMM: |y - y_oracle| <= 1e-5 * sum |a||x| element by element;
 * GCN layer (bf16 matrix cores): |y - y_oracle| <= 1e-2 * |A| (|X| |W|).
 """
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -539,3 +541,56 @@ def test_walk_records_of_four_and_eight_bytes(dg, device, m):
     pat = dg.arw_patterns(*to_dev(g, device), 7, k, d)     # one walk per lane on the row pointers
     ref = pat.amax(dim=2).to(torch.int64).sum(dim=1).cpu().numpy()
     assert np.array_equal(S.astype(np.int64), ref)
+
+
+def test_schedule_of_long_rows(dg, device):
+    """Rows of 16 copy tiles and parts and just more, of more than a wavefront has lanes, several
+    to a wavefront of the sorted order, among short and empty ones: every row of the SpMM, also
+    with the long rows in the sparse region (tiles without parts)."""
+    gen = np.random.default_rng(29)
+    n = 3000
+    long_rows = [16384, 16385, 17408, 17409, 20000, 70000, 100000, 300000] + [33000] * 20
+    rows = [gen.integers(0, n, gen.integers(0, 6)).tolist() for _ in range(n)]
+    for i, m in enumerate(long_rows):
+        rows[100 * i + 3] = gen.integers(0, n, m).tolist()
+    g = small.from_rows(rows)
+    g.val[:] = gen.standard_normal(g.val.size).astype(np.float32)
+    assert 1 << 20 <= g.col.size < 1 << 23           # copy tiles of 1,024 entries, parts of 512
+    X = dense.features_normal(n, 32, seed=4, stream_id=44)
+    Xd = torch.from_numpy(X).to(device)
+    Yr, B = oracle.spmm(g, X)
+    for force in ("auto", "sparse"):
+        plan = dg.Plan(*to_dev(g, device), seed=2, walks_per_node=4, walk_len=3, force_mode=force)
+        info = plan.info()
+        if force == "auto":
+            parts = [(int(d) + 511) // 512 for d in np.diff(g.rowptr) if d > 512]
+            assert info["n_split_rows"] == len(long_rows) == len(parts)
+            assert info["n_split_parts"] == sum(parts)
+        Y = torch.full((n, 32), float("nan"), dtype=torch.float32, device=device)
+        dg.spmm(plan, Xd, Y)
+        assert_spmm_close(Y.cpu().numpy(), Yr, B, what=f"long rows, {force}")
+        plan.destroy()
+
+
+def test_plan_of_one_row_costs_no_more_than_of_short_rows(dg, device):
+    """2^23 - 2^10 entries in one row of 2^16 nodes, and spread over them: the same bytes to copy.
+    One thread that listed the row's copy tiles and parts took the plan to twice the time."""
+    n, m = 1 << 16, (1 << 23) - (1 << 10)
+    gen = torch.Generator(device=device).manual_seed(3)
+    col = torch.randint(0, n, (m,), device=device, dtype=torch.int32, generator=gen)
+    val = torch.ones(m, dtype=torch.float32, device=device)
+    spread = (torch.arange(n + 1, device=device) * m // n).to(torch.int32)
+    one = torch.zeros(n + 1, dtype=torch.int32, device=device)
+    one[n // 3:] = m
+    times = []
+    for rp in (spread, one):
+        best = float("inf")
+        for _ in range(10):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            dg.Plan(rp, col, val, seed=0, walks_per_node=4, walk_len=3).destroy()
+            torch.cuda.synchronize()
+            best = min(best, 1e3 * (time.perf_counter() - t))
+        times.append(best)
+    print("plan of spread rows, of one row (ms):", times)
+    assert times[1] <= 1.5 * times[0], times
