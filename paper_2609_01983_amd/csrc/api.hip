@@ -6,7 +6,6 @@
 #include <mutex>
 #include <string>
 #include <new>
-#include <vector>
 
 #include "internal.h"
 
@@ -84,23 +83,36 @@ int alloc_bytes(void **p, size_t bytes) {
 
 // ---- cached device blocks
 //
-// A plan takes one large block and its build one scratch block.  Released blocks are
-// kept (at most kCachedBlocks) and handed out again to a request of at
-// most their size and at least half of it, so that rebuilding a plan of the same
-// matrix does not pay hipMalloc and hipFree of gigabytes every time.  A full cache gives the
-// block released longest ago back to HIP: when it kept its first blocks instead, a program
-// that went on to other matrices paid both calls twice per plan (partition and SpMM of 63M
-// entries, n = 2^21, after plans of smaller graphs: 22.6 ms instead of 6.3).  A failed
-// hipMalloc first returns the device's cached blocks and tries again.
+// A plan takes one large block and its build one scratch block.  Released blocks are kept and
+// handed out again to a request of at most their size and at least half of it, so that
+// rebuilding a plan of the same matrix does not pay hipMalloc and hipFree of gigabytes every
+// time.  The blocks released last stay as long as they are together at most kCachedBytes (6% of
+// the device's memory) and kCachedBlocks, and the last kCachedMin whatever their size (two
+// plans of any size); what was released before them goes back to HIP.  By count alone a
+// program that rebuilds plans of a few sizes in turn pays both calls on every build (plans of n =
+// 2^17, 2^19 and 2^20 in turn, four blocks: 3,370 us when the oldest goes, 2,800 when the newest
+// goes; by bytes 1,900), and when the newest goes, so does one that went on to other matrices.
+// A failed hipMalloc first returns the device's cached blocks and tries again.
 namespace {
 struct CachedBlock {
     int device;
     size_t bytes;
     void *ptr;
 };
-std::mutex g_cache_mu;
-std::vector<CachedBlock> g_cache;
-constexpr size_t kCachedBlocks = 4;
+constexpr size_t kCachedBytes = size_t{16} << 30;
+constexpr size_t kCachedBlocks = 64;
+constexpr size_t kCachedMin = 4;
+std::mutex g_cache_mu;                        // guards the three below
+CachedBlock g_cache[kCachedBlocks];           // in the order of release, oldest first
+size_t g_cache_count = 0, g_cache_bytes = 0;
+
+void *take_cached(size_t i) {                 // lock held
+    void *p = g_cache[i].ptr;
+    g_cache_bytes -= g_cache[i].bytes;
+    --g_cache_count;
+    for (; i < g_cache_count; ++i) g_cache[i] = g_cache[i + 1];
+    return p;
+}
 }  // namespace
 
 int alloc_block(void **p, size_t *capacity, size_t bytes) {
@@ -113,34 +125,30 @@ int alloc_block(void **p, size_t *capacity, size_t bytes) {
     if (st) return st;
     {
         std::lock_guard<std::mutex> lock(g_cache_mu);
-        size_t best = g_cache.size();
-        for (size_t i = 0; i < g_cache.size(); ++i) {
+        size_t best = g_cache_count;
+        for (size_t i = 0; i < g_cache_count; ++i) {
             const CachedBlock &b = g_cache[i];
             if (b.device == dev && b.bytes >= bytes && b.bytes / 2 <= bytes &&
-                (best == g_cache.size() || b.bytes < g_cache[best].bytes))
+                (best == g_cache_count || b.bytes < g_cache[best].bytes))
                 best = i;
         }
-        if (best < g_cache.size()) {
-            *p = g_cache[best].ptr;
+        if (best < g_cache_count) {
             *capacity = g_cache[best].bytes;
-            g_cache.erase(g_cache.begin() + static_cast<std::ptrdiff_t>(best));
+            *p = take_cached(best);
             return DUALGCN_OK;
         }
     }
     hipError_t e = hipMalloc(p, bytes);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
-        std::vector<void *> drop;
+        void *drop[kCachedBlocks];
+        size_t drops = 0;
         {
             std::lock_guard<std::mutex> lock(g_cache_mu);
-            for (size_t i = g_cache.size(); i-- > 0;) {
-                if (g_cache[i].device == dev) {
-                    drop.push_back(g_cache[i].ptr);
-                    g_cache.erase(g_cache.begin() + static_cast<std::ptrdiff_t>(i));
-                }
-            }
+            for (size_t i = g_cache_count; i-- > 0;)
+                if (g_cache[i].device == dev) drop[drops++] = take_cached(i);
         }
-        for (void *q : drop) (void)hipFree(q);
+        for (size_t i = 0; i < drops; ++i) (void)hipFree(drop[i]);
         e = hipMalloc(p, bytes);
     }
     if (e != hipSuccess) {
@@ -155,17 +163,20 @@ int alloc_block(void **p, size_t *capacity, size_t bytes) {
 void release_block(void *p, size_t capacity) {
     if (!p) return;
     int dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        std::lock_guard<std::mutex> lock(g_cache_mu);
-        void *oldest = nullptr;
-        if (g_cache.size() >= kCachedBlocks) {
-            oldest = g_cache.front().ptr;
-            g_cache.erase(g_cache.begin());
-        }
-        g_cache.push_back(CachedBlock{dev, capacity, p});      // released order, oldest first
-        p = oldest;
+    if (hipGetDevice(&dev) != hipSuccess) {
+        (void)hipFree(p);
+        return;
     }
-    if (p) (void)hipFree(p);
+    void *drop[kCachedBlocks];
+    size_t drops = 0;
+    {
+        std::lock_guard<std::mutex> lock(g_cache_mu);
+        if (g_cache_count == kCachedBlocks) drop[drops++] = take_cached(0);
+        g_cache[g_cache_count++] = CachedBlock{dev, capacity, p};
+        g_cache_bytes += capacity;
+        while (g_cache_count > kCachedMin && g_cache_bytes > kCachedBytes) drop[drops++] = take_cached(0);
+    }
+    for (size_t i = 0; i < drops; ++i) (void)hipFree(drop[i]);
 }
 
 }  // namespace dgc
