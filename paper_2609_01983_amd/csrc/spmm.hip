@@ -325,15 +325,16 @@ __device__ __forceinline__ void gather(const Args &a, const Round<LPR, MODE> &r,
             as[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(r.v[(U0 + u) / LPR])));
             // an invalid entry reads the row of the last one and drops it
             const bool ok = (row & kNoRow) == 0;
-            load_x<VEC>(a.X + static_cast<int64_t>(row & kRowMask) * a.ld + (fin ? f : 0), xs[u]);
+            load_x<VEC>(a.X + static_cast<int64_t>(row & kRowMask) * a.ld + (fin ? f : a.f0), xs[u]);
 #pragma unroll
             for (int j = 0; j < VEC; ++j) xs[u][j] = ok ? xs[u][j] : 0.f;
         }
     } else {
-        // a lane without features of its own reads the row's first ones, which nothing uses
+        // a lane without features of its own reads the window's first ones, which nothing uses and
+        // other lanes read (the row's first: another line per entry, F = 300 on n = 2^20 10% slower)
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(a.X), 0, static_cast<int>(a.x_bytes), 0x00020000);
-        const uint32_t lane_off = fin ? static_cast<uint32_t>(f) * 4u : 0u;
+        const uint32_t lane_off = static_cast<uint32_t>(fin ? f : a.f0) * 4u;
 #pragma unroll
         for (int u = 0; u < Q; ++u) {
             const int src = base4 + ((U0 + u) % LPR) * 4;
