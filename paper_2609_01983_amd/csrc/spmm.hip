@@ -216,34 +216,43 @@ struct StageRows {
     }
 };
 
-// Cache classes of the gathers (kernels instantiated with CP): a gathered row is read
+// Cache classes of the gathers (kernels instantiated with kClasses): a gathered row is read
 // with the default policy when its column is among the hottest (rows the L2s keep), and
 // non-temporal otherwise, so that rows read a few times per launch do not push the hot
 // rows out of the L2.  The plan marks the other columns with bit 31 of the sorted copy's
-// column (a column is below 2^31 - 1, so a marked one never reads as the invalid -1);
-// every kernel masks it off, and it never changes which row is read.
+// column (columns are below 2^31); every kernel masks it off, and it never changes which
+// row is read.
 constexpr int kCpolNt = 2;                    // the nt field of a gfx950 buffer load
 constexpr uint32_t kRowMask = 0x7FFFFFFFu;
 
-// How a launch's gathers address X, and how many are requested at a time.
-//   kBuffer   buffer loads at 32-bit byte offsets (X up to kMaxBufferBytes), a round of 16
-//   kHalves   the same, half a round, for operands that only the memory-side cache holds
-//   kClasses  the same as kHalves with the cache classes above, for larger operands
-//   kWide     64-bit addresses, half a round
-// A round at once puts 8 MiB of requested lines per XCD in flight (16 wavefronts a CU), twice
-// its L2, and each request takes the place of a line: half a round hides the latency as well
-// once the operand misses the L2 anyway.  Measured on R-MAT graphs, a round / half (us):
-// classes F = 64, n = 2^22 2060 / 2030, n = 2^21 1709 / 1681; F = 128, n = 2^22 4073 / 4046;
-// the fused kernel 128 -> 64, n = 2^22 3980 / 3944.  Operands of 128 to 256 MiB, F = 64: n =
-// 2^20 437 / 425, 700,000 (17.5M entries) 406 / 397; below, a round wins (n = 2^19 190 / 197;
-// block model n = 2^18, F = 128 424 / 458).  The sums are the same either way.
-enum GatherMode { kBuffer = 0, kClasses = 1, kWide = 2, kHalves = 3 };
+// How a launch's gathers address X.
+//   kBuffer   buffer loads at 32-bit byte offsets (X up to kMaxBufferBytes)
+//   kClasses  the same with the cache classes above
+//   kWide     64-bit addresses
+enum GatherMode { kBuffer = 0, kClasses = 1, kWide = 2 };
 
-// Dynamic LDS that keeps a CU to four workgroups where the registers would let five or six in
-// (five / four groups, us: kHalves, n = 2^20, F = 64 433 / 425; kClasses with rows of 33 to 64
-// lanes, n = 2^20, F = 128 whole 927 / 861, F = 256 whole 2158 / 1898; kWide, n = 2^22, F = 256
-// 9160 / 8968; classes in 16-lane groups keep five: n = 2^21, F = 128 3309 / 3376).
-constexpr unsigned kFourGroupsLds = 38 * 1024;
+// How many gathers a lane group requests at a time (kRound, a half or a quarter of it) and how
+// many workgroups a CU holds (0: as many as fit); see pick_gathers.
+struct Gathers {
+    int mode, q, groups;
+};
+
+// Dynamic LDS that keeps a CU to `groups` workgroups whose kernel has `own` bytes of its own.
+constexpr unsigned kCuLds = 160 * 1024;
+constexpr unsigned groups_lds(int groups, unsigned own) {
+    return groups == 0 ? 0 : kCuLds / static_cast<unsigned>(groups) - 2048 - own;
+}
+constexpr bool keeps(int groups) {
+    const unsigned each = groups_lds(groups, 0);
+    return groups * each <= kCuLds && (groups + 1) * each > kCuLds;
+}
+static_assert(keeps(4) && keeps(5), "the padding holds what it says");
+
+// LDS for the sums of a long row's other wavefronts: launches that share rows (see share_rows).
+template <int LPR, int VEC, int MODE>
+constexpr int shared_sums() {
+    return MODE == kBuffer ? (kWaves - 1) * LPR * VEC : 1;
+}
 
 // Offset of an entry that reads nothing: past the end of every buffer, also with a feature's
 // offset (below 4 MiB) added, so that a buffer load of it returns zeros.
@@ -351,44 +360,41 @@ __device__ __forceinline__ void gather(const Args &a, const Round<LPR, MODE> &r,
     }
 }
 
+// Entries U0 .. kRound - 1 of a round that starts at e, Q gathers requested at a time; the next
+// round's columns and values are requested behind the round's last gathers.
+template <int LPR, int VEC, int MODE, int Q, int U0, bool PF, class Term>
+__device__ __forceinline__ void round_terms(const Args &a, Round<LPR, MODE> &r, int32_t e, int32_t e1, int32_t step,
+                                            int li, int gbase, int f, bool fin, const Term &term) {
+    {
+        float as[Q], xs[Q][VEC];
+        gather<LPR, VEC, MODE, U0, Q>(a, r, gbase, f, fin, as, xs);
+        if constexpr (PF && U0 + Q == kRound) r.load(a, e + step, e1, li);
+#pragma unroll
+        for (int u = 0; u < Q; ++u) term(e + U0 + u, as[u], xs[u]);
+    }
+    if constexpr (U0 + Q < kRound) {
+        __builtin_amdgcn_sched_barrier(0);       // the next gathers stay behind
+        if (e + U0 + Q < e1)
+            round_terms<LPR, VEC, MODE, Q, U0 + Q, PF>(a, r, e, e1, step, li, gbase, f, fin, term);
+    }
+}
+
 // A lane group's walk over the rounds of kRound entries at e0, e0 + step, ... below e1:
 // term(e, weight, slice) for every entry in order (entries past e1 come with weight and
 // slice zero), flush() after every round.  The next round's columns and values are requested
 // behind the current round's gathers (not for groups of one or two lanes, which hold 16 or 8
 // of them in registers: a wavefront less per SIMD).
-template <int LPR, int VEC, int MODE, class Term, class Flush>
+template <int LPR, int VEC, int MODE, int Q, class Term, class Flush>
 __device__ __forceinline__ void walk_rounds(const Args &a, int32_t e0, int32_t e1, int32_t step, int li,
                                             int gbase, int f, bool fin, const Term &term, const Flush &flush) {
     if (e0 >= e1) return;
-    constexpr int Q = MODE == kBuffer ? kRound : kRound / 2;   // gathers requested at a time
     constexpr bool PF = LPR >= 4;
     Round<LPR, MODE> r;
     if constexpr (PF) r.load(a, e0, e1, li);
     for (int32_t e = e0; e < e1; e += step) {
         if constexpr (!PF) r.load(a, e, e1, li);
         r.ready(a, e, e1, li);
-        if constexpr (Q == kRound) {
-            float as[Q], xs[Q][VEC];
-            gather<LPR, VEC, MODE, 0, Q>(a, r, gbase, f, fin, as, xs);
-            if constexpr (PF) r.load(a, e + step, e1, li);
-#pragma unroll
-            for (int u = 0; u < Q; ++u) term(e + u, as[u], xs[u]);
-        } else {
-            {
-                float as[Q], xs[Q][VEC];
-                gather<LPR, VEC, MODE, 0, Q>(a, r, gbase, f, fin, as, xs);
-#pragma unroll
-                for (int u = 0; u < Q; ++u) term(e + u, as[u], xs[u]);
-            }
-            __builtin_amdgcn_sched_barrier(0);       // the second half's gathers stay behind
-            if (e + Q < e1) {
-                float as[Q], xs[Q][VEC];
-                gather<LPR, VEC, MODE, Q, Q>(a, r, gbase, f, fin, as, xs);
-                if constexpr (PF) r.load(a, e + step, e1, li);
-#pragma unroll
-                for (int u = 0; u < Q; ++u) term(e + Q + u, as[u], xs[u]);
-            }
-        }
+        round_terms<LPR, VEC, MODE, Q, 0, PF>(a, r, e, e1, step, li, gbase, f, fin, term);
         flush();
     }
 }
@@ -396,7 +402,7 @@ __device__ __forceinline__ void walk_rounds(const Args &a, int32_t e0, int32_t e
 // Dense path: a lane group's sums over its rounds of one row, in V = 1, 2 or 4 chains (round q
 // of the group adds to chain q % V, by rotating them) that are then added pairwise: as (0 + 2)
 // + (1 + 3) for four, whichever chain is first after the last rotation.
-template <int LPR, int VEC, int MODE, int V>
+template <int LPR, int VEC, int MODE, int Q, int V>
 __device__ __forceinline__ void dense_rounds(const Args &a, int32_t e0, int32_t e1, int32_t step, int li,
                                              int gbase, int f, bool fin, double (&tot)[VEC]) {
     float acc[VEC];
@@ -407,7 +413,7 @@ __device__ __forceinline__ void dense_rounds(const Args &a, int32_t e0, int32_t 
 #pragma unroll
         for (int q = 0; q < V; ++q) chain[q][j] = 0.0;
     }
-    walk_rounds<LPR, VEC, MODE>(
+    walk_rounds<LPR, VEC, MODE, Q>(
         a, e0, e1, step, li, gbase, f, fin,
         [&](int32_t, float w, const float (&x)[VEC]) {
 #pragma unroll
@@ -437,15 +443,15 @@ __device__ __forceinline__ void dense_rounds(const Args &a, int32_t e0, int32_t 
 // groups have one each, two 32-lane groups two each, a whole wavefront all four -- one after
 // the other where a round's gathers leave no registers for four sets of sums.  So the SpMM's slices of 64 features and the
 // fused kernel, which reads rows whole, add a long row in the same order and give the same bits.
-template <int LPR, int VEC, int MODE>
+template <int LPR, int VEC, int MODE, int Q>
 __device__ __forceinline__ void long_row(const Args &a, int32_t e0, int32_t e1, int wave, int waves, int li,
                                          int gw, int gbase, int f, bool fin, double (&tot)[VEC]) {
-    if constexpr (VEC == 4 && LPR == 64 && MODE == kBuffer) {
+    if constexpr (VEC == 4 && LPR == 64 && MODE == kBuffer && Q == kRound) {
         double even[VEC], t[VEC];
 #pragma unroll 1
         for (int q = 0; q < 4; ++q) {                       // chains 0, 2, 1, 3
             const int chain = (q >> 1) | ((q & 1) << 1);
-            dense_rounds<LPR, VEC, MODE, 1>(a, e0 + (chain * waves + wave) * kRound, e1, 4 * waves * kRound, li,
+            dense_rounds<LPR, VEC, MODE, Q, 1>(a, e0 + (chain * waves + wave) * kRound, e1, 4 * waves * kRound, li,
                                             gbase, f, fin, t);
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
@@ -456,7 +462,7 @@ __device__ __forceinline__ void long_row(const Args &a, int32_t e0, int32_t e1, 
         return;
     }
     constexpr int GPW = 64 / LPR;
-    dense_rounds<LPR, VEC, MODE, VEC == 4 && LPR >= 32 ? LPR / 16 : 1>(
+    dense_rounds<LPR, VEC, MODE, Q, VEC == 4 && LPR >= 32 ? LPR / 16 : 1>(
         a, e0 + (gw * waves + wave) * kRound, e1, GPW * waves * kRound, li, gbase, f, fin, tot);
 #pragma unroll
     for (int m = 32; m >= LPR; m >>= 1)
@@ -477,7 +483,7 @@ __device__ __forceinline__ int32_t task_meta(const int32_t (&m)[N], int j, int g
 // The work of logical workgroup lb (feature slice `slice`) for wavefront `wave` of a
 // workgroup of WAVES wavefronts; finished rows go to `emit`.  red: (WAVES - 1) x LPR x VEC
 // float64 of LDS, used where wavefronts share a row.
-template <int LPR, int VEC, int WAVES, int MODE, class Emit>
+template <int LPR, int VEC, int WAVES, int MODE, int Q, class Emit>
 __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int wave,
                                            const Emit &emit, double *red) {
     constexpr int GPW = 64 / LPR;                 // lane groups per wavefront
@@ -497,14 +503,14 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
         const int64_t i = a.n - a.n_long - 1 - gi;
         if (i < a.n_sparse) return;           // the whole group leaves together
         double tot[VEC];
-        dense_rounds<LPR, VEC, MODE, 1>(a, a.pptr[i], a.pptr[i + 1], kRound, li, gbase, f, fin, tot);
+        dense_rounds<LPR, VEC, MODE, Q, 1>(a, a.pptr[i], a.pptr[i + 1], kRound, li, gbase, f, fin, tot);
         emit.row(a.perm[i], gw * kTaskRows, tot, f, fin);
         return;
     }
     if (lb < a.nb_parts + a.nb_long) {
         // ---------------- dense path, long rows and parts of split rows: a wavefront each, or
         // the workgroup's wavefronts together
-        constexpr bool kMayShare = MODE == kBuffer || MODE == kHalves;
+        constexpr bool kMayShare = MODE == kBuffer;
         const bool share = kMayShare && a.coop && lb < a.nb_parts + a.nb_coop;
         int32_t i, e0, e1;
         int part = -1, first = 0;
@@ -526,7 +532,7 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
             if (e1 - e0 > a.dense_chunk) return;   // covered by its parts
         }
         double tot[VEC];
-        long_row<LPR, VEC, MODE>(a, e0, e1, share ? wave : 0, share ? WAVES : 1, li, gw, gbase, f, fin, tot);
+        long_row<LPR, VEC, MODE, Q>(a, e0, e1, share ? wave : 0, share ? WAVES : 1, li, gw, gbase, f, fin, tot);
         if constexpr (kMayShare) {
             if (share) {
                 // every wavefront of the workgroup is here with the same row: the first adds
@@ -589,7 +595,7 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
         tot[j] = 0.0;
         part[j] = 0.f;
     }
-    walk_rounds<LPR, VEC, MODE>(
+    walk_rounds<LPR, VEC, MODE, Q>(
         a, e_begin, e_end, kRound, li, gbase, f, fin,
         [&](int32_t e, float w, const float (&x)[VEC]) {
 #pragma unroll
@@ -618,11 +624,11 @@ __device__ __forceinline__ void spmm_block(const Args &a, int lb, int slice, int
         });
 }
 
-template <int LPR, int VEC, bool BF, int MODE>
+template <int LPR, int VEC, bool BF, int MODE, int Q>
 __global__ __launch_bounds__(kThreads) void spmm_dual_kernel(const Args a) {
     const StoreRows<VEC, BF> emit{a.Y, a.ld, a.relu != 0};
-    __shared__ double red[MODE == kBuffer || MODE == kHalves ? (kWaves - 1) * LPR * VEC : 1];
-    spmm_block<LPR, VEC, kWaves, MODE>(
+    __shared__ double red[shared_sums<LPR, VEC, MODE>()];
+    spmm_block<LPR, VEC, kWaves, MODE, Q>(
         a, static_cast<int>(blockIdx.x) / a.S, static_cast<int>(blockIdx.x) % a.S,
         static_cast<int>(threadIdx.x) >> 6, emit, red);
 }
@@ -692,7 +698,7 @@ size_t xw_lds_bytes(int lpr, int K, int N) {
            (xw_stage_in_tile(K) ? 0 : static_cast<size_t>(kWaves) * kXwStageWords * sizeof(float));
 }
 
-template <int LPR, int MODE>
+template <int LPR, int MODE, int Q>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void spmm_xw_kernel(const Args a, const float *__restrict__ W,
                                                            float *__restrict__ T, int32_t K,
@@ -709,7 +715,7 @@ void spmm_xw_kernel(const Args a, const float *__restrict__ W,
     const bool stage_in_tile = xw_stage_in_tile(K);
     float *stage_own = reinterpret_cast<float *>(reinterpret_cast<int32_t *>(xw_lds + (N + kWaves * ROWS) * ld) +
                                                  kWaves * ROWS) + wave * kXwStageWords;
-    __shared__ double red[MODE == kBuffer ? (kWaves - 1) * LPR * 4 : 1];
+    __shared__ double red[shared_sums<LPR, 4, MODE>()];
     stage_w<kThreads>(wt, ld, W, N, K, N);
     if (lane < ROWS) outs[lane] = -1;
     __syncthreads();
@@ -717,7 +723,7 @@ void spmm_xw_kernel(const Args a, const float *__restrict__ W,
     const StageRows emit{h, outs, ld, a.relu != 0, lane % LPR == 0, static_cast<unsigned short *>(a.Y), a.ld};
     constexpr int KF = LPR / 8;               // A fragments of a row: K <= 4 LPR, 32 k each
     for (int lb = static_cast<int>(blockIdx.x); lb < nblocks; lb += static_cast<int>(gridDim.x)) {
-        spmm_block<LPR, 4, kWaves, MODE>(a, lb, 0, wave, emit, red);
+        spmm_block<LPR, 4, kWaves, MODE, Q>(a, lb, 0, wave, emit, red);
         __syncwarp();
         // the lane's MFMA coordinates, recomputed here (hidden from the optimiser) rather
         // than held in registers through the aggregation
@@ -828,13 +834,13 @@ int64_t schedule_blocks(Args &a) {
     return static_cast<int64_t>(a.nb_parts) + a.nb_dense + nb_sparse;
 }
 
-template <int LPR, int MODE>
+template <int LPR, int MODE, int Q>
 int launch_xw_window(Args a, const float *W, float *T, int32_t K, int32_t N, hipStream_t s) {
     const int64_t blocks = schedule_blocks<LPR>(a);
     if (blocks > 0x7FFFFFFF) return DUALGCN_ERR_UNSUPPORTED;
     if (blocks > 0) {
         const size_t lds = xw_lds_bytes(LPR, K, N);
-        const void *kern = reinterpret_cast<const void *>(&spmm_xw_kernel<LPR, MODE>);
+        const void *kern = reinterpret_cast<const void *>(&spmm_xw_kernel<LPR, MODE, Q>);
         if (lds > 64 * 1024) {
             const int st = hip_status(hipFuncSetAttribute(
                 kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
@@ -847,7 +853,7 @@ int launch_xw_window(Args a, const float *W, float *T, int32_t K, int32_t N, hip
         const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2048 / kThreads, (160 * 1024) / lds));
         const int64_t grid = std::min<int64_t>(
             blocks, std::max<int64_t>(per_cu * device_cus(), (blocks + kXwBlocksPerGroup - 1) / kXwBlocksPerGroup));
-        hipLaunchKernelGGL((spmm_xw_kernel<LPR, MODE>), dim3(static_cast<unsigned>(grid)), dim3(kThreads),
+        hipLaunchKernelGGL((spmm_xw_kernel<LPR, MODE, Q>), dim3(static_cast<unsigned>(grid)), dim3(kThreads),
                            lds, s, a, W, T, K, N, static_cast<int32_t>(blocks));
     }
     if (a.n_parts > 0)
@@ -856,30 +862,41 @@ int launch_xw_window(Args a, const float *W, float *T, int32_t K, int32_t N, hip
     return hip_status(hipGetLastError());
 }
 
-template <int LPR, int VEC, int MODE>
-int launch_dual(Args a, bool bf, hipStream_t s) {
+template <int LPR, int VEC, int MODE, int Q>
+int launch_dual(Args a, int groups, bool bf, hipStream_t s) {
     const int64_t blocks = schedule_blocks<LPR>(a) * a.S;
-    constexpr unsigned lds = MODE == kHalves || MODE == kWide || (MODE == kClasses && LPR >= 32) ? kFourGroupsLds : 0;
     if (blocks == 0) return DUALGCN_OK;
     if (blocks > 0x7FFFFFFF) return DUALGCN_ERR_UNSUPPORTED;
+    constexpr unsigned own = shared_sums<LPR, VEC, MODE>() * sizeof(double);
+    static_assert(own < groups_lds(5, 0), "the padding goes on top of the kernel's own LDS");
+    const unsigned lds = groups_lds(groups, own);
     if (bf)
-        hipLaunchKernelGGL((spmm_dual_kernel<LPR, VEC, true, MODE>), dim3(static_cast<unsigned>(blocks)),
+        hipLaunchKernelGGL((spmm_dual_kernel<LPR, VEC, true, MODE, Q>), dim3(static_cast<unsigned>(blocks)),
                            dim3(kThreads), lds, s, a);
     else
-        hipLaunchKernelGGL((spmm_dual_kernel<LPR, VEC, false, MODE>), dim3(static_cast<unsigned>(blocks)),
+        hipLaunchKernelGGL((spmm_dual_kernel<LPR, VEC, false, MODE, Q>), dim3(static_cast<unsigned>(blocks)),
                            dim3(kThreads), lds, s, a);
     return DUALGCN_OK;
 }
 
 template <int LPR, int VEC>
-int launch_window(Args a, int mode, bool bf, hipStream_t s) {
-    constexpr int CLS = LPR >= 8 && VEC == 4 ? kClasses : kBuffer;   // classes: rows of whole 128-byte lines
-    constexpr int HLV = (LPR == 16 || LPR == 64) && VEC == 4 ? kHalves : kBuffer;
-    int st;
-    if (mode == kWide) st = launch_dual<LPR, VEC, kWide>(a, bf, s);
-    else if (mode == kHalves && HLV == kHalves) st = launch_dual<LPR, VEC, HLV>(a, bf, s);
-    else if (mode == CLS) st = launch_dual<LPR, VEC, CLS>(a, bf, s);
-    else st = launch_dual<LPR, VEC, kBuffer>(a, bf, s);
+int launch_window(const Args &a, const Gathers &g, bool bf, hipStream_t s) {
+    constexpr int kHalf = kRound / 2, kQuarter = kRound / 4;
+    int st = DUALGCN_ERR_UNSUPPORTED;
+    if (g.mode == kWide) {
+        st = launch_dual<LPR, VEC, kWide, VEC == 1 ? kHalf : kRound>(a, g.groups, bf, s);
+    } else if (g.mode == kClasses) {
+        if constexpr (VEC == 4 && LPR >= 32)
+            if (g.q == kQuarter) st = launch_dual<LPR, VEC, kClasses, kQuarter>(a, g.groups, bf, s);
+        if constexpr (VEC == 4 && LPR >= 8)
+            if (g.q == kHalf) st = launch_dual<LPR, VEC, kClasses, kHalf>(a, g.groups, bf, s);
+    } else if (g.q == kRound) {
+        st = launch_dual<LPR, VEC, kBuffer, kRound>(a, g.groups, bf, s);
+    } else {
+        if constexpr (VEC == 4 && LPR >= 16)
+            st = g.q == kHalf ? launch_dual<LPR, VEC, kBuffer, kHalf>(a, g.groups, bf, s)
+                              : launch_dual<LPR, VEC, kBuffer, kQuarter>(a, g.groups, bf, s);
+    }
     if (st) return st;
     if (a.n_parts > 0) {
         if (bf)
@@ -932,20 +949,27 @@ int long_row_class(int lpr, int mode, int32_t w) {
     return cls;
 }
 
+// Operands from which a launch of many long rows is bound by the lines it has in flight (see
+// pick_gathers).
+constexpr uint64_t kThrottleBytes = 88ull << 20;
+
+// Are the rows of at least 2^kLongRowOctave entries and the parts of split rows no more than the
+// CUs?  Then a workgroup each starts at once (share_rows), and the launch waits for them; with
+// more of them it is bound by what its gathers request.
+bool few_long_rows(const Plan &p) { return p.n_long[0] + p.n_split_parts <= device_cus(); }
+
 // Do a workgroup's wavefronts share each long row?  On small graphs the longest row is the whole
 // launch: a wavefront takes a row of 4,000 entries in 63 rounds (64 features), four
-// together in 16.  Rows of at least 2^kLongRowOctave entries and the parts of split rows are
-// shared while there are no more of them than CUs, so that all of them start at once;
-// beyond that the chip is full without (n = 2^19, 1,160 long rows, F = 128: 409 us alone, 430
-// shared).  Measured (us) alone / shared: n = 30,007, 120 long rows, F = 64 57 / 22, F = 96
-// 103 / 39; n = 20,001, 18 rows, F = 64 24 / 16; n = 2^17, F = 64 (154 split rows) 37.6 / 38.4.
+// together in 16.  Beyond as many such rows and parts as CUs the chip is full without (n = 2^19,
+// 1,160 long rows, F = 128: 409 us alone, 430 shared; n = 2^17, 154 long rows and 420 parts, F = 64
+// 37.6 / 38.4).  Measured (us) alone / shared: n = 30,007, 120 long rows, F = 64 57 / 22, F = 96
+// 103 / 39; n = 20,001, 18 rows, F = 64 24 / 16.
 // By the plan and the addressing alone, so the fused kernel and the SpMM add a row alike.
 void share_rows(const Plan &p, int mode, Args &a) {
-    const bool share = (mode == kBuffer || mode == kHalves) && p.n_long[0] + p.n_split_parts <= device_cus();
+    const bool share = mode == kBuffer && few_long_rows(p);
     a.coop = share ? 1 : 0;
     a.n_coop = share ? p.n_long[0] : 0;
 }
-
 
 // A window of 128, 192 or 256 features whose rows are whole 128-byte lines is cut into slices
 // of 64 features, and workgroup b takes slice b % S: workgroups go to the XCDs in turn, so
@@ -962,29 +986,59 @@ bool sliced_window(int32_t ld, int32_t w) {
     return w > 64 && w % 64 == 0 && ld % 32 == 0;
 }
 
-// Cache classes of a launch's gathers (the plan marks every column outside the hottest
-// kHotRows; classes apply from operands larger than the 256 MiB memory-side cache, below
-// which non-temporal loads would only lose rows that cache holds).  Measured on R-MAT
+// Addressing.  Cache classes: the plan marks every column outside the hottest kHotRows; they
+// apply from operands larger than the 256 MiB memory-side cache, below which non-temporal loads
+// would only lose rows that cache holds, and where rows fill whole 128-byte lines (more than 16
+// features).  Measured on R-MAT
 // graphs with shuffled ids (c5: n = 2^22, 67M entries; c4: n = 2^21, 63M entries),
 // F = 128: the layer-1 aggregation fused with the next update 4.27 -> 4.03 ms (c5) and
 // 3.72 -> 3.45 ms (c4), the plain SpMM 4.46 -> 4.24 and 3.70 -> 3.47 ms; the L2 hit rate of
 // the fused kernel rose from 22.5% to 26.8% and its fetched bytes fell from 28.6 to 27.0 GB.
 // Hot sets of 16 MiB or less, or a third class loading warm rows with sc0, were slower.
 //
-// gather_mode sets the buffer's size in `a` and picks the addressing for gathers of w features
-// of rows ld apart: 64-bit addresses when X is too large for a buffer load's 32-bit offsets;
-// classes when the plan marked its cold columns, rows are read whole with 16-byte loads, and X
-// is larger than the memory-side cache; half rounds when it is larger than half that cache (on
-// plans that mark no columns only where rows take a wavefront's whole width).
-int gather_mode(const Plan &p, int32_t ld, int32_t w, bool vec, Args &a) {
+// Gathers in flight.  16 gathers requested at once by 16 wavefronts a CU are up to 8 MiB of lines
+// per XCD, twice its L2, and each request takes the place of a line: where many rows are long
+// and the launch is bound by its gathers, fewer in flight are faster.  A short launch waits for
+// a part of a split row instead (a chunk's round trips one after the other, four times as many
+// in quarter rounds): `deep` says that the launch outlasts it.  Measured on R-MAT graphs of
+// degree 5 to 60, n = 20,001 to 2^22, block models and rows of equal length; us, round / half with four
+// workgroups a CU / quarter with four:
+//   to kThrottleBytes     n = 90,000, 2.8M entries, F = 200 (68 MiB) 203 / 186 / 192; n = 131,072, 8.0M,
+//                         F = 160 (80 MiB) 401 / 344 / 343
+//   above                 n = 131,072, 8.0M, F = 200 (100 MiB) 616 / 536 / 489; n = 262,143, 16M, F = 100
+//                         579 / 574 / 528; n = 2^19, 16.3M, F = 64 337 / 334 / 315
+//   above, not deep       n = 2^19, 8.4M, F = 72 285 / 281 / 305
+//   few long rows         n = 20,001, 0.2M, F = 100 22 / 22 / 29; block model n = 2^18, F = 200 798 / 771 /
+//                         807, F = 64 208 / 205 / 220
+//   classes, 65-96        (half with four / half with five / quarter with five) n = 2^20, 16.8M, F = 96 695
+//                         / 681 / 674; n = 750,000, 12M 490 / 475 / 529
+//   classes, 97-128       n = 2^20, 16.8M, F = 120 1,051 / 1,051 / 989; n = 2^22, F = 100 3,085 / 3,085 / 3,054
+//   classes, 129-192      n = 2^20, F = 160 1,183 / 1,172 / 1,299
+//   classes, 193-256      n = 2^21, 65M, F = 200 6,830 / 6,764 / 6,299; not deep: n = 2^19, 8.4M 875 / 884 / 991
+// 16-lane groups under classes, and 8-lane ones, keep half a round and every workgroup that fits;
+// narrower groups a round (their lines are few).  64-bit addresses: a round (round / half with four:
+// n = 8.4M, F = 132 7,183 / 7,311, n = 70M, F = 16 5,098 / 5,192), half of it with one feature a lane
+// (n = 358M, F = 3 29.4 ms; four workgroups a CU 44.3), a quarter in the fused kernel (half / quarter:
+// 256 -> 32, n = 2^22 8,870 / 8,557; 128 -> 64, n = 8.4M 10,126 / 9,970).  The sums are the same throughout.
+Gathers pick_gathers(const Plan &p, int32_t ld, int32_t w, int lpr, Args &a) {
+    constexpr int kHalf = kRound / 2, kQuarter = kRound / 4;
     const uint64_t bytes = static_cast<uint64_t>(p.n) * static_cast<uint64_t>(ld) * sizeof(float);
-    if (bytes > kMaxBufferBytes) return kWide;
+    if (bytes > kMaxBufferBytes) return {kWide, kRound, 0};
     a.x_bytes = static_cast<uint32_t>(bytes);
-    const bool whole = w > 128 && !sliced_window(ld, w);      // a wavefront per row piece
-    if (!vec || !(p.cold_marked || whole)) return kBuffer;
     const uint64_t operand = static_cast<uint64_t>(p.n) * static_cast<uint64_t>(w) * sizeof(float);
-    if (p.cold_marked && operand > kGatherClassMinBytes) return kClasses;
-    return operand > kGatherClassMinBytes / 2 ? kHalves : kBuffer;
+    const bool classes = w > 16 && p.cold_marked && operand > kGatherClassMinBytes;
+    if (lpr < 16) return classes ? Gathers{kClasses, kHalf, 0} : Gathers{kBuffer, kRound, 0};
+    const bool deep = p.nnz >= int64_t{2560} * p.dense_chunk;
+    if (classes) {
+        if (lpr == 16) return {kClasses, kHalf, 0};
+        if (w <= 96) return {kClasses, kHalf, 5};
+        return {kClasses, deep && (w <= 128 || w > 192) ? kQuarter : kHalf, 4};
+    }
+    if (!few_long_rows(p)) return {kBuffer, deep && operand > kThrottleBytes ? kQuarter : kHalf, 4};
+    // few long rows: half a round only where the operand is larger than half the memory-side cache
+    // (and, in 16-lane groups, the plan's columns are marked)
+    const bool half = operand > kGatherClassMinBytes / 2 && (lpr == 64 || (lpr == 16 && p.cold_marked));
+    return half ? Gathers{kBuffer, kHalf, 4} : Gathers{kBuffer, kRound, 0};
 }
 
 }  // namespace
@@ -1036,14 +1090,17 @@ int launch_spmm_xw(const Plan &p, const float *X, const float *W, float *T, void
     a.S = 1;
     a.sw = F_in;
     const int lpr = window_lpr(F_in);
-    const int mode = gather_mode(p, F_in, F_in, true, a);
-    a.n_long = p.n_long[long_row_class(lpr, mode, F_in)];
-    share_rows(p, mode, a);
+    const Gathers g = pick_gathers(p, F_in, F_in, lpr, a);
+    a.n_long = p.n_long[long_row_class(lpr, g.mode, F_in)];
+    share_rows(p, g.mode, a);
     auto launch = [&](auto width) {
         constexpr int LPR = decltype(width)::value;
-        if (mode == kWide) return launch_xw_window<LPR, kWide>(a, W, T, F_in, F_out, s);
-        if (mode == kClasses) return launch_xw_window<LPR, kClasses>(a, W, T, F_in, F_out, s);
-        return launch_xw_window<LPR, kBuffer>(a, W, T, F_in, F_out, s);
+        // half a round under classes whatever the width: rows are read whole here, and four
+        // workgroups a CU at most fit
+        if (g.mode == kWide) return launch_xw_window<LPR, kWide, kRound / 4>(a, W, T, F_in, F_out, s);
+        if (g.mode == kClasses) return launch_xw_window<LPR, kClasses, kRound / 2>(a, W, T, F_in, F_out, s);
+        if (g.q == kRound) return launch_xw_window<LPR, kBuffer, kRound>(a, W, T, F_in, F_out, s);
+        return launch_xw_window<LPR, kBuffer, kRound / 2>(a, W, T, F_in, F_out, s);
     };
     int st = DUALGCN_ERR_UNSUPPORTED;
     if (lpr == 8) st = launch(std::integral_constant<int, 8>());
@@ -1077,24 +1134,23 @@ int launch_spmm(const Plan &p, const float *X, void *Y, int32_t F, bool relu, bo
             const int lpr = sliced_window(F, w) ? 16 : window_lpr(w);
             a.sw = 4 * lpr;
             a.S = (w + a.sw - 1) / a.sw;
-            // cache classes for the widths whose rows fill whole 128-byte lines
-            const int mode = gather_mode(p, F, w, w > 16, a);
-            a.n_long = p.n_long[long_row_class(lpr, mode, w)];
-            share_rows(p, mode, a);
-            if (lpr == 1) st = launch_window<1, 4>(a, mode, bf, s);
-            else if (lpr == 2) st = launch_window<2, 4>(a, mode, bf, s);
-            else if (lpr == 4) st = launch_window<4, 4>(a, mode, bf, s);
-            else if (lpr == 8) st = launch_window<8, 4>(a, mode, bf, s);
-            else if (lpr == 16) st = launch_window<16, 4>(a, mode, bf, s);
-            else if (lpr == 32) st = launch_window<32, 4>(a, mode, bf, s);
-            else st = launch_window<64, 4>(a, mode, bf, s);
+            const Gathers g = pick_gathers(p, F, w, lpr, a);
+            a.n_long = p.n_long[long_row_class(lpr, g.mode, w)];
+            share_rows(p, g.mode, a);
+            if (lpr == 1) st = launch_window<1, 4>(a, g, bf, s);
+            else if (lpr == 2) st = launch_window<2, 4>(a, g, bf, s);
+            else if (lpr == 4) st = launch_window<4, 4>(a, g, bf, s);
+            else if (lpr == 8) st = launch_window<8, 4>(a, g, bf, s);
+            else if (lpr == 16) st = launch_window<16, 4>(a, g, bf, s);
+            else if (lpr == 32) st = launch_window<32, 4>(a, g, bf, s);
+            else st = launch_window<64, 4>(a, g, bf, s);
         } else {
             // F < 4: one feature per lane
             a.sw = 64;
             a.S = (w + 63) / 64;
-            const int mode = gather_mode(p, F, w, false, a);
-            share_rows(p, mode, a);
-            st = launch_window<64, 1>(a, mode, bf, s);
+            const Gathers g = pick_gathers(p, F, w, 1, a);
+            share_rows(p, g.mode, a);
+            st = launch_window<64, 1>(a, g, bf, s);
         }
     }
     if (st) return st;
