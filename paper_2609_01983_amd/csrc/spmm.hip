@@ -971,8 +971,8 @@ void share_rows(const Plan &p, int mode, Args &a) {
     a.n_coop = share ? p.n_long[0] : 0;
 }
 
-// A window of 128, 192 or 256 features whose rows are whole 128-byte lines is cut into slices
-// of 64 features, and workgroup b takes slice b % S: workgroups go to the XCDs in turn, so
+// A window of 128 or 256 features whose rows are whole 128-byte lines is cut into slices
+// of 64 features, and workgroup b takes slice b % S: workgroups go to the 8 XCDs in turn, so
 // an XCD reads every second (or fourth) 256-byte piece of the rows and its 4 MiB L2 keeps twice
 // (four times) as many of the hottest rows.  Each slice reads the columns and values again
 // (8 bytes an entry against 256 gathered).  Measured, whole rows and slices of 64 (us):
@@ -980,10 +980,17 @@ void share_rows(const Plan &p, int mode, Args &a) {
 //            n = 2^21 3475 / 3331, n = 2^22 4201 / 4059
 //   F = 256  n = 2^19 1036 / 860, 1.5M 2315 / 2048, n = 2^21 7891 / 7053
 // Slices of 32 features, whose wavefronts walk eight rows side by side, lose it again (F = 128,
-// n = 2^22: 4542).  Where slices would share lines or leave lanes idle whole rows win (1.5M
-// nodes, F = 96 788 / 929, F = 100 1048 / 1492, F = 160 1371 / 1592, F = 200 1949 / 2531).
-bool sliced_window(int32_t ld, int32_t w) {
-    return w > 64 && w % 64 == 0 && ld % 32 == 0;
+// n = 2^22: 4542).  Three slices (F = 192) do too, since eight XCDs taken in turn see all three
+// (n = 2^20, 16.8M entries 1430 / 1570; n = 2^22 4,670 / 4,890), except on small launches that wait
+// for a long row, where slices are more wavefronts (n = 20,001, 0.3M entries 49 / 29).  So do slices
+// that share lines or leave lanes idle (1.5M nodes, F = 96 788 / 929, F = 100 1048 / 1492, F = 160
+// 1371 / 1592, F = 200 1949 / 2531).  Operands that only memory holds gain nothing without hot rows either: every row
+// of 30 entries, n = 400,000, F = 256 2,215 / 2,424; of 20, n = 2^20, F = 128 2,056 / 2,115.
+bool sliced_window(const Plan &p, int32_t ld, int32_t w) {
+    if ((w != 128 && w != 192 && w != 256) || ld % 32 != 0) return false;
+    const uint64_t operand = static_cast<uint64_t>(p.n) * w * sizeof(float);
+    if (w == 192) return few_long_rows(p) && operand <= kThrottleBytes;
+    return p.n_long[0] > 0 || operand <= kGatherClassMinBytes;
 }
 
 // Addressing.  Cache classes: the plan marks every column outside the hottest kHotRows; they
@@ -1131,7 +1138,7 @@ int launch_spmm(const Plan &p, const float *X, void *Y, int32_t F, bool relu, bo
         if (vec) {
             // the smallest power-of-two lane group with 4 features per lane that holds the
             // window, or slices of 64 features (see sliced_window)
-            const int lpr = sliced_window(F, w) ? 16 : window_lpr(w);
+            const int lpr = sliced_window(p, F, w) ? 16 : window_lpr(w);
             a.sw = 4 * lpr;
             a.S = (w + a.sw - 1) / a.sw;
             const Gathers g = pick_gathers(p, F, w, lpr, a);
