@@ -327,17 +327,28 @@ __device__ __forceinline__ void gather(const Args &a, const Round<LPR, MODE> &r,
     int base4 = gbase * 4;
     asm volatile("" : "+v"(base4));
     if constexpr (MODE == kWide) {
+        uint32_t row[Q];
 #pragma unroll
         for (int u = 0; u < Q; ++u) {
             const int src = base4 + ((U0 + u) % LPR) * 4;
-            const uint32_t row = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, r.c[(U0 + u) / LPR]));
+            row[u] = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, r.c[(U0 + u) / LPR]));
             as[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(r.v[(U0 + u) / LPR])));
-            // an invalid entry reads the row of the last one and drops it
-            const bool ok = (row & kNoRow) == 0;
-            load_x<VEC>(a.X + static_cast<int64_t>(row & kRowMask) * a.ld + (fin ? f : a.f0), xs[u]);
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) xs[u][j] = ok ? xs[u][j] : 0.f;
         }
+#pragma unroll
+        for (int u = 0; u < Q; ++u)
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) xs[u][j] = 0.f;
+        // an invalid entry reads the row of the last one and drops it; with one feature a lane (F < 4)
+        // most lanes have none and stay out (n = 358M, F = 3, one entry a row 30.7 ms, so 28.6)
+        if (VEC != 1 || fin) {
+#pragma unroll
+            for (int u = 0; u < Q; ++u)
+                load_x<VEC>(a.X + static_cast<int64_t>(row[u] & kRowMask) * a.ld + (fin ? f : a.f0), xs[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < Q; ++u)
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) xs[u][j] = (row[u] & kNoRow) == 0 ? xs[u][j] : 0.f;
     } else {
         // a lane without features of its own reads the window's first ones, which nothing uses and
         // other lanes read (the row's first: another line per entry, F = 300 on n = 2^20 10% slower)
@@ -1025,7 +1036,7 @@ bool sliced_window(const Plan &p, int32_t ld, int32_t w) {
 // 16-lane groups under classes, and 8-lane ones, keep half a round and every workgroup that fits;
 // narrower groups a round (their lines are few).  64-bit addresses: a round (round / half with four:
 // n = 8.4M, F = 132 7,183 / 7,311, n = 70M, F = 16 5,098 / 5,192), half of it with one feature a lane
-// (n = 358M, F = 3 29.4 ms; four workgroups a CU 44.3), a quarter in the fused kernel (half / quarter:
+// (n = 358M, F = 3 28.6 ms; four workgroups a CU 44.3), a quarter in the fused kernel (half / quarter:
 // 256 -> 32, n = 2^22 8,870 / 8,557; 128 -> 64, n = 8.4M 10,126 / 9,970).  The sums are the same throughout.
 Gathers pick_gathers(const Plan &p, int32_t ld, int32_t w, int lpr, Args &a) {
     constexpr int kHalf = kRound / 2, kQuarter = kRound / 4;
