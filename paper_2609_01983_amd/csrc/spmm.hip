@@ -1142,8 +1142,11 @@ int launch_spmm(const Plan &p, const float *X, void *Y, int32_t F, bool relu, bo
     const bool vec = F >= 4;
     a.fcap = vec ? F - 4 : 0x7FFFFFFF - 4;
     int st = DUALGCN_OK;
-    for (int32_t f0 = 0; f0 < F && !st; f0 += kMaxSlice) {
-        const int32_t w = F - f0 < kMaxSlice ? F - f0 : kMaxSlice;
+    for (int32_t f0 = 0, w = 0; f0 < F && !st; f0 += w) {
+        // a window's last lane takes its last four features, so a window holds at least four: one
+        // to three features past a multiple of kMaxSlice get four of the window before them
+        w = std::min(F - f0, kMaxSlice);
+        if (vec && F - f0 > w && F - f0 - w < 4) w -= 4;
         a.f0 = f0;
         a.fend = f0 + w;
         if (vec) {

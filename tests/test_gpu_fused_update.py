@@ -279,3 +279,34 @@ def test_odd_widths_and_unaligned_rows(dg, device, F, shift):
         # the sum's bound, and a bfloat16 store's half unit in the last place
         assert np.all(np.abs(Y - Yr) <= 1e-5 * B * (1 + u) + u * np.abs(Yr))
         assert torch.all(out[:shift] == 7.0) and torch.all(out[shift + g.n * F:] == 7.0)
+
+
+@pytest.mark.parametrize("F", [257, 258, 259, 513, 515])
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_windows_do_not_share_features(dg, device, F, dt):
+    """One to three features past a multiple of 256: the last window takes four more features
+    instead of computing some of the window before it again, so features that hold the same
+    numbers get the same bits in it.  The long rows' second halves are the negatives of the
+    first, of magnitudes 2^-30 to 2^30 from one round of 16 to the next, so what is left of the
+    float64 sums is their rounding, which shows the order of additions."""
+    gen = np.random.default_rng(37)
+    n, lens = 1500, [96, 160, 320, 640, 1024, 2048, 4096]
+    rows = [gen.integers(0, n, gen.integers(0, 5)).tolist() for _ in range(n)]
+    for i, m in enumerate(lens):
+        rows[9 * i] = gen.integers(0, n, m // 2).tolist() * 2
+    g = small.from_rows(rows)
+    g.val[:] = gen.standard_normal(g.val.size).astype(np.float32)
+    for i, m in enumerate(lens):
+        e = int(g.rowptr[9 * i])
+        g.val[e:e + m // 2] *= np.exp2(np.repeat(gen.integers(-30, 31, m // 32), 16)).astype(np.float32)
+        g.val[e + m // 2:e + m] = -g.val[e:e + m // 2]
+    X = torch.from_numpy(dense.features_normal(n, F, seed=F, stream_id=42)).to(device)
+    f0 = F // 256 * 256 - 4
+    X[:, f0:] = X[:, f0:f0 + 1]
+    plan = dg.Plan(*to_dev(g, device), seed=1, walks_per_node=4, walk_len=3)
+    Y = dg.spmm(plan, X, out_bf16=dt == torch.bfloat16)
+    assert torch.equal(Y[:, f0:], Y[:, f0:f0 + 1].expand(-1, F - f0))
+    Yr, B = oracle.spmm(g, X.cpu().numpy())
+    u = 2.0 ** -8 if dt == torch.bfloat16 else 0.0
+    assert np.all(np.abs(Y.double().cpu().numpy() - Yr) <= 1e-5 * B * (1 + u) + u * np.abs(Yr))
+    plan.destroy()
