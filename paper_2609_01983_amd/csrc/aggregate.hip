@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kThreads) void aggregator_search_kernel(const int32
                                                                      int32_t *__restrict__ bad,
                                                                      float *__restrict__ val) {
     const int64_t e = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    if (e >= nnz) return;
+    if (e >= nnz || (*bad & 1)) return;        // row pointers out of order
     int32_t lo = 0, hi = n;                    // the last r in [lo, hi) with rowptr[r] <= e
     while (hi - lo > 1) {
         const int32_t mid = lo + (hi - lo) / 2;

@@ -84,6 +84,20 @@ def test_aggregator_tiles(dg, device, n, lengths, kind):
     assert _ulps(v[finite], ref[finite]).max(initial=0) <= 1
 
 
+@pytest.mark.parametrize("n,per_row", [(1000, 5), (1 << 16, 4), ((1 << 16) + 1, 4), (100000, 7)])
+@pytest.mark.parametrize("kind", ["gcn", "mean", "sum"])
+def test_row_pointers_out_of_order_leave_the_values_alone(dg, device, n, per_row, kind):
+    """On both sides of the bound between the search per entry (up to 2^18 entries) and the tiles."""
+    g = _tiles(n, [per_row], 7)
+    rp, c = _dev(g, device)
+    rp[n // 2] += 2 * per_row                         # within the entries, above its successor
+    val = torch.full((c.numel(),), 7.0, device=device)
+    with pytest.raises(dg.DualGCNError) as e:
+        dg.aggregator_values(rp, c, kind, val=val)
+    assert e.value.status == dg.ERR_BAD_CSR
+    assert torch.all(val == 7.0)
+
+
 def _ms(call):
     """Shortest of ten calls, each waited for."""
     best = float("inf")
