@@ -4,8 +4,9 @@ hottest 65,536 (bit 31 of its sorted copy's columns), and an SpMM whose operand 
 depend on either.  A sparse graph of 2^18 + 7 nodes with 64 hub rows (56 of about 800 entries,
 one wavefront each, and 8 of about 12,000 split into parts of the plan's 1024-entry chunk) keeps
 the oracle fast
-while an F = 256 operand (256 MiB + 7 KiB) takes the class path of the plain SpMM
-(spmm_dual_kernel<64, 4, *, true>) and of the fused junction (spmm_xw_kernel<64, true>).
+while an F = 256 operand (256 MiB + 7 KiB) takes the class path of the plain SpMM, in slices of
+64 features, and of the fused junction, which reads rows whole (test_gpu_gather_variants.py has the
+other widths).
 The aggregation is the one of Sec. 1 and Sec. 2.1; every row is checked against the oracle
 within 1e-5 sum |a||x| (F = 256: the class path; F = 128, a 128 MiB operand: the plain path)."""
 import ctypes

@@ -289,8 +289,25 @@ def test_windows_do_not_share_features(dg, device, F, dt):
     numbers get the same bits in it.  The long rows' second halves are the negatives of the
     first, of magnitudes 2^-30 to 2^30 from one round of 16 to the next, so what is left of the
     float64 sums is their rounding, which shows the order of additions."""
-    gen = np.random.default_rng(37)
-    n, lens = 1500, [96, 160, 320, 640, 1024, 2048, 4096]
+    g = _rounding_rows(0, seed=37)
+    X = torch.from_numpy(dense.features_normal(g.n, F, seed=F, stream_id=42)).to(device)
+    f0 = F // 256 * 256 - 4
+    X[:, f0:] = X[:, f0:f0 + 1]
+    plan = dg.Plan(*to_dev(g, device), seed=1, walks_per_node=4, walk_len=3)
+    Y = dg.spmm(plan, X, out_bf16=dt == torch.bfloat16)
+    assert torch.equal(Y[:, f0:], Y[:, f0:f0 + 1].expand(-1, F - f0))
+    Yr, B = oracle.spmm(g, X.cpu().numpy())
+    u = 2.0 ** -8 if dt == torch.bfloat16 else 0.0
+    assert np.all(np.abs(Y.double().cpu().numpy() - Yr) <= 1e-5 * B * (1 + u) + u * np.abs(Yr))
+    plan.destroy()
+
+
+def _rounding_rows(extra, seed):
+    """Rows of 96 to 4,097 entries, and `extra` of 600, whose second halves are the negatives of the
+    first, of magnitudes 2^-30 to 2^30 from one round of 16 to the next: what is left of their
+    float64 sums is rounding, which depends on the order of additions."""
+    gen = np.random.default_rng(seed)
+    n, lens = 3000, [96, 160, 320, 512, 640, 1024, 2048, 4096, 4128] + [640] * extra
     rows = [gen.integers(0, n, gen.integers(0, 5)).tolist() for _ in range(n)]
     for i, m in enumerate(lens):
         rows[9 * i] = gen.integers(0, n, m // 2).tolist() * 2
@@ -300,13 +317,22 @@ def test_windows_do_not_share_features(dg, device, F, dt):
         e = int(g.rowptr[9 * i])
         g.val[e:e + m // 2] *= np.exp2(np.repeat(gen.integers(-30, 31, m // 32), 16)).astype(np.float32)
         g.val[e + m // 2:e + m] = -g.val[e:e + m // 2]
-    X = torch.from_numpy(dense.features_normal(n, F, seed=F, stream_id=42)).to(device)
-    f0 = F // 256 * 256 - 4
-    X[:, f0:] = X[:, f0:f0 + 1]
+    return g
+
+
+@pytest.mark.parametrize("extra", [0, 300])
+@pytest.mark.parametrize("F_in", [32, 64, 96, 128, 160, 192, 224, 256])
+def test_fused_and_two_calls_add_long_rows_in_one_order(dg, device, extra, F_in):
+    """The order itself: long rows shared by a workgroup or a wavefront each, in slices of 64 features
+    and whole, a round and half a round of gathers at a time, all parts of split rows."""
+    g = _rounding_rows(extra, seed=F_in)
     plan = dg.Plan(*to_dev(g, device), seed=1, walks_per_node=4, walk_len=3)
-    Y = dg.spmm(plan, X, out_bf16=dt == torch.bfloat16)
-    assert torch.equal(Y[:, f0:], Y[:, f0:f0 + 1].expand(-1, F - f0))
-    Yr, B = oracle.spmm(g, X.cpu().numpy())
-    u = 2.0 ** -8 if dt == torch.bfloat16 else 0.0
-    assert np.all(np.abs(Y.double().cpu().numpy() - Yr) <= 1e-5 * B * (1 + u) + u * np.abs(Yr))
+    Xd = torch.from_numpy(dense.features_normal(g.n, F_in, seed=F_in, stream_id=43)).to(device)
+    Wd = torch.from_numpy(_weights(F_in, 32, seed=5)).to(device)
+    T = torch.empty((g.n, 32), dtype=torch.float32, device=device)
+    st = dg.lib().dualgcn_spmm_update(plan.handle, Xd.data_ptr(), Wd.data_ptr(), T.data_ptr(), None,
+                                      F_in, 32, dg.RELU, ctypes.c_void_p(0))
+    torch.cuda.synchronize()
+    assert st == dg.OK
+    assert torch.equal(T, _two_calls(dg, plan, Xd, Wd, True))
     plan.destroy()
