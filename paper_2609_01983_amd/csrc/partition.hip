@@ -463,9 +463,10 @@ __global__ __launch_bounds__(kThreads) void scan_apply_kernel(const uint32_t *in
 // Sort tiles hold kThreads * ITEMS keys: 16 per thread on large inputs, 4 below
 // kSortSmallKeys keys, where 4096-key tiles would leave most CUs idle and make every
 // wavefront walk 16 rounds in a row (c2, 2^17 keys: 32 workgroups).  Whole plans with 16 / 4
-// keys per thread: n = 2^20 1062 / 1030 us, n = 2^21 2651 / 2624.
+// keys per thread (us): n = 2^20 471 / 447, n = 2^21 767 / 755, n = 2^22 1,448 / 1,422, n = 5.5M 1,355 /
+// 1,337, n = 8M 1,868 / 1,886.
 constexpr int kSortItemsSmall = 4;
-constexpr int64_t kSortSmallKeys = int64_t{1} << 23;
+constexpr int64_t kSortSmallKeys = int64_t{6} << 20;
 
 template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void radix_hist_kernel(const uint64_t *__restrict__ keys,
@@ -1222,7 +1223,10 @@ int build_plan(const dualgcn_csr *csr, uint64_t seed, uint32_t k, uint32_t d,
     // walk kernel, 1.2M entries, 50 walks of 30 steps 468 -> 286 us, 1.3M entries, 16 of 5 40.5
     // -> 30.3.  With fewer bits too many steps of a power-law graph land on a node that does not
     // fit.  Plans of 50 x 30 walks, wide / packed (us): 4.2M entries (9 bits) 3358 / 2788, 8.4M
-    // (8 bits) 6990 / 6614, 16.8M (7 bits) 13830 / 16308.
+    // (8 bits) 6990 / 6614, 16.8M (7 bits) 13830 / 16308.  Rows of equal length, also where every
+    // degree is looked up: 80,000 of 100 (9 bits) 2208 / 1988, 40,000 of 300 (8 bits) 1284 / 1166, 15,000 of
+    // 1,000 (8 bits, 600 x 12) 2138 / 1944; the one slower case met: R-MAT n = 200,000, 16.2M (8 bits)
+    // 4415 / 4555.
     constexpr uint32_t kPackedDegreeBits = 8;
     const uint32_t first_bits = static_cast<uint32_t>(std::max(bit_length(static_cast<uint64_t>(nnz)), bit_length(static_cast<uint64_t>(n))));
     const uint32_t succ_shift = use_succ && first_bits + kPackedDegreeBits <= 32 ? first_bits : 0;

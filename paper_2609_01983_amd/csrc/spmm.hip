@@ -30,7 +30,8 @@
 // Gathers.  A group takes the entries of its row (or task) in rounds of 16:
 // each lane loads 16 / LPR (column, value) pairs with coalesced loads, the
 // pairs are broadcast inside the group with shuffles, and all 16 neighbour
-// slices (eight on large operands) are requested before the first product, so every group
+// slices (a half or a quarter of them where the launch is bound by its gathers: pick_gathers)
+// are requested before the first product, so every group
 // keeps that many loads in flight (the ILP of the paper's dense path, Alg. 1, deepened).
 // Nothing in a round branches (see gather), and the next round's pairs are requested with this
 // round's slices.
