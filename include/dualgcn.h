@@ -204,7 +204,7 @@ int dualgcn_plan_load(const dualgcn_csr *csr, const void *buf, size_t bytes, voi
  * float64, and each output is rounded once to float32, so results do not
  * depend on timing (bit-reproducible for a given plan and F).  On plans that mark
  * cold columns (dualgcn_plan_info.cold_marked) and X larger than 256 MiB and
- * smaller than 4 GiB, rows of X outside the hottest 65,536 are read with
+ * at most 4 GiB - 8 MiB, rows of X outside the hottest 65,536 are read with
  * non-temporal loads, which keeps the hottest rows in the L2; the results are the
  * same.  1 <= F < 2^20.  Asynchronous.
  */
@@ -482,7 +482,7 @@ typedef struct dualgcn_plan_info {
                                 the shorter dense rows get a lane group each) */
     int32_t cold_marked;     /* 1 when the plan marks the columns outside the hottest
                                 65,536 (plans of more than 2^18 nodes): an SpMM whose
-                                operand is larger than 256 MiB and smaller than 4 GiB then
+                                operand is larger than 256 MiB and at most 4 GiB - 8 MiB then
                                 gathers their rows with non-temporal loads (same results) */
 } dualgcn_plan_info;
 

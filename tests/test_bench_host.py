@@ -86,7 +86,7 @@ def test_committed_counter_summary_names_the_default_kernel():
     columns and the 2 GiB operand is within the classes' range)."""
     text = open(bench.COUNTER_SUMMARY).read()
     cp = bench.gather_classes({"cold_marked": 1}, 1 << 22, 128)
-    assert "workload: c5" in text and f"kernel: spmm_xw_kernel<32, {'true' if cp else 'false'}>" in text
+    assert "workload: c5" in text and f"kernel: spmm_xw_kernel{' with cache classes' if cp else ''}\n" in text
 
 
 @pytest.mark.parametrize("gpus", ["2", "8"])
@@ -101,12 +101,14 @@ def test_more_than_one_gpu_is_refused(gpus):
 def test_gather_class_rule_names_the_kernel_that_runs():
     """The bench names the instantiation the library launches: cache classes only on plans
     that marked their cold columns, for rows of more than 16 floats, with the operand above
-    the 256 MiB memory-side cache and within the 4 GiB a buffer load addresses."""
+    the 256 MiB memory-side cache and within the 4 GiB - 8 MiB a gather's offset addresses."""
     marked, unmarked = {"cold_marked": 1}, {"cold_marked": 0}
     n5 = 1 << 22
     assert bench.gather_classes(marked, n5, 128)          # c5 layer 1: 2 GiB
     assert bench.gather_classes(marked, n5, 64)           # c5 layer 2: 1 GiB
     assert not bench.gather_classes(marked, n5, 256)      # 4 GiB: beyond 32-bit offsets
+    assert not bench.gather_classes(marked, 8380000, 128)  # 4 GiB - 4.2 MiB: an invalid entry's offset
+    assert bench.gather_classes(marked, 8370000, 128)     # 4 GiB - 9.1 MiB
     assert not bench.gather_classes(unmarked, n5, 128)
     assert not bench.gather_classes(marked, n5, 16)       # rows of a quarter line
     assert not bench.gather_classes(marked, 1 << 17, 64)  # 32 MiB: fits the memory-side cache
