@@ -994,14 +994,15 @@ void share_rows(const Plan &p, int mode, Args &a) {
 // Slices of 32 features, whose wavefronts walk eight rows side by side, lose it again (F = 128,
 // n = 2^22: 4542).  Three slices (F = 192) do too, since eight XCDs taken in turn see all three
 // (n = 2^20, 16.8M entries 1430 / 1570; n = 2^22 4,670 / 4,890), except on small launches that wait
-// for a long row, where slices are more wavefronts (n = 20,001, 0.3M entries 49 / 29).  So do slices
+// for a few long rows, where slices are more wavefronts (n = 20,001, 0.3M entries 49 / 29, n = 131,072,
+// 0.8M 97 / 79; equal rows of 30 415 / 428).  So do slices
 // that share lines or leave lanes idle (1.5M nodes, F = 96 788 / 929, F = 100 1048 / 1492, F = 160
 // 1371 / 1592, F = 200 1949 / 2531).  Operands that only memory holds gain nothing without hot rows either: every row
 // of 30 entries, n = 400,000, F = 256 2,215 / 2,424; of 20, n = 2^20, F = 128 2,056 / 2,115.
 bool sliced_window(const Plan &p, int32_t ld, int32_t w) {
     if ((w != 128 && w != 192 && w != 256) || ld % 32 != 0) return false;
     const uint64_t operand = static_cast<uint64_t>(p.n) * w * sizeof(float);
-    if (w == 192) return few_long_rows(p) && operand <= kThrottleBytes;
+    if (w == 192) return few_long_rows(p) && operand <= kGatherClassMinBytes / 2;
     return p.n_long[0] > 0 || operand <= kGatherClassMinBytes;
 }
 
@@ -1069,10 +1070,15 @@ size_t spmm_xw_lds_bytes(int32_t F_in, int32_t F_out) {
 // The fused junction pays where the aggregation is bound by the memory fabric: the
 // operand is larger than the memory-side cache (then the n x F_in intermediate it never
 // writes or reads back is traffic saved), and the kernel's LDS still lets at least
-// kFusedMinGroups workgroups share a CU.  Measured (F_in -> F_out): R-MAT c4 (n = 2^21)
-// 128 -> 64 fused 3.42 ms against 3.66 ms for the two calls, 64 -> 32 1.76 against 1.85;
-// the SBM c3 (n = 2^18, 128 MiB operand) 0.76 against 0.62 and R-MAT c2 (n = 2^17) 0.33
-// against 0.29; 256 -> 128, where one workgroup fills a CU's LDS, 16.0 against 7.85 ms (c4).
+// kFusedMinGroups workgroups share a CU.  Measured (F_in -> F_out, fused / the two calls, us), R-MAT
+// n = 2^20 (16.8M entries), n = 2^21 (65M), n = 2^22 (67M):
+//   128 -> 64   900 / 941, 3,452 / 3,495, 3,937 / 4,334
+//    64 -> 32   (256 MiB: two calls) 441 / 464, 1,761 / 1,786, 2,050 / 2,186
+//   192 -> 32   1,352 / 1,478, 5,203 / 5,499, 5,895 / 6,660; 192 -> 64 1,511 / 1,513, 5,364 / 5,710, 6,356 / 6,836
+//   256 -> 32   1,829 / 1,884, 7,041 / 7,109, 8,465 / 9,287
+//   160 -> 32   1,159 / 1,260, 4,279 / 4,665, 4,975 / 5,600; 160 -> 64 1,398 / 1,292, 4,801 / 4,658, 5,837 / 5,796
+//   256 -> 64   (two groups: two calls) 2,140 / 1,922, 7,451 / 7,202, 9,409 / 9,417
+// and n = 2^18 (4.2M, below the cache) 128 -> 64 257 / 191, 256 -> 32 450 / 375.
 constexpr int kFusedMinGroups = 3;
 
 bool fused_junction_pays(const Plan &p, int32_t F_in, int32_t F_out) {
