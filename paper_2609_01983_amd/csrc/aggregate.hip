@@ -24,10 +24,21 @@ constexpr int kThreads = 256;
 // which the validation then need not read.
 constexpr int kTile = 2048;
 constexpr int kPer = kTile / kThreads;
-// Up to this many entries a search per entry is as fast: every entry is in flight at once, and
-// the tiles' launch and barriers cost more (whole GCN calls, search / tiles: 44,000 entries 36.3
-// / 37.8 us, 320,000 40.1 / 38.4, 860,000 43.4 / 40.9).
-constexpr int64_t kSearchNnz = int64_t{1} << 18;
+// A search per entry has every entry in flight at once and reads no row pointers but its own; the
+// tiles have another launch, which reads all of them, and barriers.  Whole calls (us, search / tiles,
+// GCN and mean):
+//   0.45M entries     n = 135,000 40.1 / 42.2, 38.9 / 40.0
+//   0.7M              n = 210,000 43.7 / 45.6, 41.6 / 41.8; n = 420,000 44.3 / 43.8, 42.1 / 40.6
+//                     n = 700,000 (rows of random length, 30% empty) 45.5 / 55.4, 42.9 / 52.9
+//   1M                n = 600,000 46.2 / 45.9, 43.8 / 41.4; n = 10^6 (random lengths) 60.8 / 67.9, 52.2 / 61.0
+//   2.5M              n = 2.5M 88.6 / 74.1, 73.4 / 47.1; n = 5M 100 / 109, 81.8 / 78.8; n = 12.5M 115 / 143,
+//                     89.3 / 107
+//   10M               n = 20M 291 / 326, 229 / 185; n = 50M 338 / 434, 280 / 274
+bool by_search(int kind, int64_t n, int64_t nnz) {
+    if (nnz <= int64_t{5} << 17) return true;
+    if (nnz < int64_t{5} << 18) return n >= nnz;
+    return kind == DUALGCN_AGG_GCN ? 2 * n >= 3 * nnz : n >= 4 * nnz;
+}
 
 __global__ __launch_bounds__(kThreads) void aggregator_search_kernel(const int32_t *__restrict__ rowptr,
                                                                      const int32_t *__restrict__ col, int32_t n,
@@ -180,7 +191,7 @@ int launch_aggregator_values(const dualgcn_csr *csr, int kind, float eps, int32_
     if (csr->nnz == 0) return DUALGCN_OK;
     const int64_t blocks = (csr->nnz + kTile - 1) / kTile;      // below 2^20
     const double plus = 1.0 + static_cast<double>(eps);
-    if (csr->nnz <= kSearchNnz) {
+    if (by_search(kind, csr->n, csr->nnz)) {
         hipLaunchKernelGGL(aggregator_search_kernel,
                            dim3(static_cast<unsigned>((csr->nnz + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
                            csr->rowptr, csr->col, csr->n, csr->nnz, kind, plus, bad, val);

@@ -12,6 +12,7 @@ import torch
 
 import oracle
 from graphgen import configs, dense, small
+from graphgen.csr import Graph
 
 pytestmark = pytest.mark.gpu
 
@@ -66,7 +67,7 @@ def _tiles(n, lengths, seed):
     (1, [1]), (1, [2048]), (1, [2049]), (2, [2048, 1]), (3, [0, 4096, 0]), (700, [0, 0, 0, 7, 0]),
     (5000, [0] * 999 + [3]),        # tiles that meet more rows than entries
     (4097, [1]), (300, [0, 31, 5000, 1, 2]),
-    (1 << 18, [1]), ((1 << 18) + 1, [1]),     # the last matrix searched entry by entry, the next
+    (1 << 18, [1]), ((1 << 18) + 1, [1]),
     (300000, [0, 0, 5, 0, 9, 0]),             # tiles with empty rows
     (1, [300000]), (3, [5, 290000, 7]),       # a row of more tiles than its wavefront has lanes
     (70, [32768, 32769, 3]), (130, [0, 40000]),   # rows on both sides of 16 tiles, several a wavefront
@@ -84,10 +85,34 @@ def test_aggregator_tiles(dg, device, n, lengths, kind):
     assert _ulps(v[finite], ref[finite]).max(initial=0) <= 1
 
 
+@pytest.mark.parametrize("n,lengths", [
+    (327680, [2]), (327681, [2]),              # 5 * 2^17 entries: the last searched, the next in tiles
+    (1310719, [1]), (1310720, [1]),            # below and at 5 * 2^18 entries, as many rows
+    (1400001, [0, 2]), (1966081, [1, 0, 1]),   # from there: up to 3/2 rows an entry in tiles (GCN)
+    (5242881, [1, 0, 0, 0])])                  # up to 4 (the others)
+@pytest.mark.parametrize("kind", ["gcn", "mean", "sum"])
+def test_aggregator_search_and_tiles(dg, device, n, lengths, kind):
+    """Values of matrices on both sides of the bounds between a search per entry and tiles."""
+    deg = np.resize(np.array(lengths, dtype=np.int64), n)
+    rowptr = np.zeros(n + 1, dtype=np.int32)
+    rowptr[1:] = np.cumsum(deg)
+    col = np.random.default_rng(9).integers(0, n, int(rowptr[-1])).astype(np.int32)
+    col[::7] = np.repeat(np.arange(n), deg)[::7]          # diagonal entries
+    g = Graph(n=n, rowptr=rowptr, col=col, val=np.ones(col.size, dtype=np.float32))
+    rp, c = _dev(g, device)
+    v = dg.aggregator_values(rp, c, kind, 0.25).cpu().numpy()
+    with np.errstate(divide="ignore"):
+        ref = oracle.aggregator_values(g, {"gcn": oracle.AGG_GCN, "mean": oracle.AGG_MEAN,
+                                           "sum": oracle.AGG_SUM}[kind], 0.25)
+    finite = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(v), finite)
+    assert _ulps(v[finite], ref[finite]).max(initial=0) <= 1
+
+
 @pytest.mark.parametrize("n,per_row", [(1000, 5), (1 << 16, 4), ((1 << 16) + 1, 4), (100000, 7)])
 @pytest.mark.parametrize("kind", ["gcn", "mean", "sum"])
 def test_row_pointers_out_of_order_leave_the_values_alone(dg, device, n, per_row, kind):
-    """On both sides of the bound between the search per entry (up to 2^18 entries) and the tiles."""
+    """On both sides of the bound between the search per entry (up to 5 * 2^17 entries) and the tiles."""
     g = _tiles(n, [per_row], 7)
     rp, c = _dev(g, device)
     rp[n // 2] += 2 * per_row                         # within the entries, above its successor
