@@ -46,7 +46,8 @@ __global__ __launch_bounds__(kThreads) void aggregator_search_kernel(const int32
                                                                      int32_t *__restrict__ bad,
                                                                      float *__restrict__ val) {
     const int64_t e = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    if (e >= nnz || (*bad & 1)) return;        // row pointers out of order
+    if (e >= nnz) return;
+    const int32_t flags = *bad;
     int32_t lo = 0, hi = n;                    // the last r in [lo, hi) with rowptr[r] <= e
     while (hi - lo > 1) {
         const int32_t mid = lo + (hi - lo) / 2;
@@ -55,7 +56,8 @@ __global__ __launch_bounds__(kThreads) void aggregator_search_kernel(const int32
     }
     const int32_t c = col[e];
     const double dr = static_cast<double>(rowptr[lo + 1] - rowptr[lo]);
-    double v = 0.0;
+    if (flags & 1) return;                     // row pointers out of order (looked at this late, its
+    double v = 0.0;                            // load adds no latency; the search stays in range)
     if (static_cast<uint32_t>(c) >= static_cast<uint32_t>(n)) atomicOr(bad, 2);
     else if (kind == DUALGCN_AGG_MEAN) v = 1.0 / dr;
     else if (kind == DUALGCN_AGG_SUM) v = c == lo ? one_plus_eps : 1.0;

@@ -291,7 +291,7 @@ int launch_backward_data(const void *G, bool g_bf16, const float *W, const void 
                          float *dX, int32_t n, int32_t F_in, int32_t F_out, hipStream_t stream);
 
 // ---- aggregator values (aggregate.hip): val[e] for the structure of csr.  bad: validate_csr's
-// flags (row pointers out of order: nothing is read or written); out-of-range columns read
+// flags (row pointers out of order: nothing is written); out-of-range columns read
 // nothing and set bit 2 of it, as the validation of columns does.
 int launch_aggregator_values(const dualgcn_csr *csr, int kind, float eps, int32_t *bad, float *val,
                              hipStream_t stream);
