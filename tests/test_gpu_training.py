@@ -142,6 +142,19 @@ def test_weight_grad(dg, device, n, fin, fout, xbf, gbf):
     assert np.array_equal(dW, again)
 
 
+@pytest.mark.parametrize("partials", [120, 121, 128, 129, 137, 256])
+@pytest.mark.parametrize("fin,fout", [(32, 32), (256, 256), (256, 224)])
+def test_weight_grad_partial_counts(dg, device, partials, fin, fout):
+    """Partial counts on both sides of whole batches of an eighth (16 at a time, and 4 from 2^16
+    elements: 256 -> 256), ragged last chunk."""
+    n = 64 * partials - 5
+    X = _bf16_values(dense.features_normal(n, fin, seed=fin + n))
+    G = _bf16_values(dense.features_normal(n, fout, seed=fout + 7, stream_id=7))
+    dW = dg.weight_grad(torch.from_numpy(X).to(device).to(torch.bfloat16),
+                        torch.from_numpy(G).to(device).to(torch.bfloat16)).cpu().numpy()
+    _check_rounded_operands(dW, X, G)
+
+
 def _check_rounded_operands(dW, X, G):
     """Against the exact product of the bfloat16 operands: only float32 accumulation is
     left, at most (rows per partial / 32 + 34) 2^-24 of sum |x||g| with at most 2^13 rows
