@@ -352,7 +352,7 @@ __device__ __forceinline__ void gather(const Args &a, const Round<LPR, MODE> &r,
             for (int j = 0; j < VEC; ++j) xs[u][j] = (row[u] & kNoRow) == 0 ? xs[u][j] : 0.f;
     } else {
         // a lane without features of its own reads the window's first ones, which nothing uses and
-        // other lanes read (the row's first: another line per entry, F = 300 on n = 2^20 10% slower)
+        // other lanes read (the row's first: another line per entry, F = 300 5-8% slower)
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(a.X), 0, static_cast<int>(a.x_bytes), 0x00020000);
         const uint32_t lane_off = static_cast<uint32_t>(fin ? f : a.f0) * 4u;
@@ -997,8 +997,9 @@ void share_rows(const Plan &p, int mode, Args &a) {
 // for a few long rows, where slices are more wavefronts (n = 20,001, 0.3M entries 49 / 29, n = 131,072,
 // 0.8M 97 / 79; equal rows of 30 415 / 428).  So do slices
 // that share lines or leave lanes idle (1.5M nodes, F = 96 788 / 929, F = 100 1048 / 1492, F = 160
-// 1371 / 1592, F = 200 1949 / 2531).  Operands that only memory holds gain nothing without hot rows either: every row
-// of 30 entries, n = 400,000, F = 256 2,215 / 2,424; of 20, n = 2^20, F = 128 2,056 / 2,115.
+// 1371 / 1592, F = 200 1949 / 2531).  Operands that only memory holds gain nothing without hot rows
+// either: every row of 30 entries, n = 400,000, F = 256 2,215 / 2,424; of 20, n = 2^20, F = 128
+// 2,056 / 2,115.
 bool sliced_window(const Plan &p, int32_t ld, int32_t w) {
     if ((w != 128 && w != 192 && w != 256) || ld % 32 != 0) return false;
     const uint64_t operand = static_cast<uint64_t>(p.n) * w * sizeof(float);
@@ -1027,14 +1028,14 @@ bool sliced_window(const Plan &p, int32_t ld, int32_t w) {
 //                         F = 160 (80 MiB) 401 / 344 / 343
 //   above                 n = 131,072, 8.0M, F = 200 (100 MiB) 616 / 536 / 489; n = 262,143, 16M, F = 100
 //                         579 / 574 / 528; n = 2^19, 16.3M, F = 64 337 / 334 / 315
-//   above, not deep       n = 2^19, 8.4M, F = 72 285 / 281 / 305
+//   above, not deep       n = 2^19, 8.4M, F = 72 285 / 281 / 305 (and F = 200 875 / 884 / 991 under classes)
 //   few long rows         n = 20,001, 0.2M, F = 100 22 / 22 / 29; block model n = 2^18, F = 200 798 / 771 /
 //                         807, F = 64 208 / 205 / 220
 //   classes, 65-96        (half with four / half with five / quarter with five) n = 2^20, 16.8M, F = 96 695
 //                         / 681 / 674; n = 750,000, 12M 490 / 475 / 529
 //   classes, 97-128       n = 2^20, 16.8M, F = 120 1,051 / 1,051 / 989; n = 2^22, F = 100 3,085 / 3,085 / 3,054
 //   classes, 129-192      n = 2^20, F = 160 1,183 / 1,172 / 1,299
-//   classes, 193-256      n = 2^21, 65M, F = 200 6,830 / 6,764 / 6,299; not deep: n = 2^19, 8.4M 875 / 884 / 991
+//   classes, 193-256      n = 2^21, 65M, F = 200 6,830 / 6,764 / 6,299
 // 16-lane groups under classes, and 8-lane ones, keep half a round and every workgroup that fits;
 // narrower groups a round (their lines are few).  64-bit addresses: a round (round / half with four:
 // n = 8.4M, F = 132 7,183 / 7,311, n = 70M, F = 16 5,098 / 5,192), half of it with one feature a lane
@@ -1120,9 +1121,9 @@ int launch_spmm_xw(const Plan &p, const float *X, const float *W, float *T, void
     share_rows(p, g.mode, a);
     auto launch = [&](auto width) {
         constexpr int LPR = decltype(width)::value;
-        // half a round under classes whatever the width: rows are read whole here, and four
-        // workgroups a CU at most fit
         if (g.mode == kWide) return launch_xw_window<LPR, kWide, kRound / 4>(a, W, T, F_in, F_out, s);
+        // half a round whatever the width: rows are read whole here, and at most four workgroups
+        // fit a CU
         if (g.mode == kClasses) return launch_xw_window<LPR, kClasses, kRound / 2>(a, W, T, F_in, F_out, s);
         if (g.q == kRound) return launch_xw_window<LPR, kBuffer, kRound>(a, W, T, F_in, F_out, s);
         return launch_xw_window<LPR, kBuffer, kRound / 2>(a, W, T, F_in, F_out, s);
