@@ -147,8 +147,11 @@ typedef struct dualgcn_plan dualgcn_plan;
  * The plan owns one block of device memory of about 9 nnz + 28 n bytes (S, K,
  * perm, the processing order, a copy of the matrix with its rows in that order,
  * the sparse tasks, the dense-region schedule and the partial sums of split
- * rows), released by dualgcn_plan_destroy; a scratch block is allocated and
- * released inside the call.  The processing order keeps perm's split into the
+ * rows), released by dualgcn_plan_destroy; a scratch block is taken and released
+ * inside the call.  The library keeps released blocks for later plans: the ones
+ * released last, up to 64 blocks and 16 GiB together, and the last four whatever
+ * their size.  The rest goes back to HIP, and all of the device's when an
+ * allocation of such a block runs out of memory.  The processing order keeps perm's split into the
  * sparse and the dense region; inside a region rows go by row-length octave,
  * then node id (balanced work, and the locality of the node numbering).  The
  * call waits for `stream` twice (to read the moment sums and the schedule sizes),
